@@ -54,6 +54,13 @@ inline bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_
 // one each are 3.2 rounds of the five-wave slots, the last one a fifth full).
 constexpr unsigned kDeriveWgsPerCu = 4;
 
+// ace_derive_keys_multi: from this many tiles of 256 keys per CU over all its
+// parameter sets on, a workgroup derives two tiles (one preparation for both;
+// 9 streams of 131,072 identities 322 us against 347 with one preparation per
+// tile).  Fewer tiles keep one each: every CU has its five resident workgroups
+// only up to two rounds of them.
+constexpr uint64_t kMultiStrideMin = 10;
+
 // Compute units of the current device (cached per device).
 int cu_count()
 {
@@ -132,6 +139,33 @@ inline void prof_mark(ProfCall *c, int k, hipStream_t s)
 // ------------------------------------------------------------------------------------------
 // Arguments, plan and workspace layout.
 // ------------------------------------------------------------------------------------------
+// Big-endian words of the SHA-256 padding (FIPS 180-4 sec. 5.1.1) of
+// p[0..len) || tail[0..tail_len), a message that follows `before` bytes already
+// hashed; returns the number of blocks.
+uint32_t pad_words(uint32_t *w, const uint8_t *p, size_t len, const uint8_t *tail, size_t tail_len,
+                   size_t before)
+{
+    const size_t total = len + tail_len;
+    const uint32_t blocks = (uint32_t)((total + 9 + 63) / 64);
+    memset(w, 0, 64ull * blocks);
+    auto put = [&](size_t pos, uint32_t byte) { w[pos / 4] |= byte << (24 - 8 * (pos % 4)); };
+    for (size_t i = 0; i < len; ++i) put(i, p[i]);
+    for (size_t i = 0; i < tail_len; ++i) put(len + i, tail[i]);
+    put(total, 0x80);
+    const uint64_t bits = 8ull * (before + total);
+    w[16 * blocks - 2] = (uint32_t)(bits >> 32);
+    w[16 * blocks - 1] = (uint32_t)bits;
+    return blocks;
+}
+
+// K0 of a key of at most 64 bytes (RFC 2104): its words, zero-filled.  An
+// absent salt is HashLen zero bytes (RFC 5869), the same all-zero K0.
+void key_block(uint32_t *w, const uint8_t *p, size_t len)
+{
+    memset(w, 0, 64);
+    for (size_t i = 0; i < len; ++i) w[i / 4] |= (uint32_t)p[i] << (24 - 8 * (i % 4));
+}
+
 int fill_hkdf(HkdfParams &hp, const uint8_t *salt, size_t salt_len, const uint8_t *info,
               size_t info_len)
 {
@@ -142,10 +176,10 @@ int fill_hkdf(HkdfParams &hp, const uint8_t *salt, size_t salt_len, const uint8_
     if (salt_len && !salt) return fail(ACE_ERR_INVALID_ARG, "h_salt is NULL with salt_len > 0");
     if (info_len && !info) return fail(ACE_ERR_INVALID_ARG, "h_info is NULL with info_len > 0");
     memset(&hp, 0, sizeof hp);
-    hp.salt_len = (uint32_t)salt_len;
-    hp.info_len = (uint32_t)info_len;
-    if (salt_len) memcpy(hp.salt, salt, salt_len);
-    if (info_len) memcpy(hp.info, info, info_len);
+    if (salt_len > 64) hp.salt_blocks = pad_words(hp.salt_w, salt, salt_len, nullptr, 0, 0);
+    else key_block(hp.salt_w, salt, salt_len);
+    const uint8_t one = 0x01;
+    hp.info_blocks = pad_words(hp.info_w, info, info_len, &one, 1, 64);
     return ACE_OK;
 }
 
@@ -671,7 +705,7 @@ ACE_API int ace_derive_keys_multi(const uint8_t *d_rev, uint32_t n_id,
     if (!aligned(d_rev, 4) || (d_key_out && !aligned(d_key_out, 4)) || (d_mid_out && !aligned(d_mid_out, 4)))
         return fail(ACE_ERR_INVALID_ARG, "misaligned device array");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    const unsigned gx = (unsigned)((n_id + kWG - 1) / kWG);
+    const uint64_t tiles = (n_id + kWG - 1ull) / kWG;
     for (uint32_t first = 0; first < n_streams; first += kMultiStreams) {
         MultiHkdf mp;
         memset(&mp, 0, sizeof mp);
@@ -679,11 +713,12 @@ ACE_API int ace_derive_keys_multi(const uint8_t *d_rev, uint32_t n_id,
         mp.count = std::min<uint32_t>(kMultiStreams, n_streams - first);
         for (uint32_t y = 0; y < mp.count; ++y) {
             const ace_hkdf_stream &t = h_streams[first + y];
-            mp.s[y].salt_len = (uint32_t)t.salt_len;
-            mp.s[y].info_len = (uint32_t)t.info_len;
-            if (t.salt_len) memcpy(mp.s[y].salt, t.h_salt, t.salt_len);
-            if (t.info_len) memcpy(mp.s[y].info, t.h_info, t.info_len);
+            key_block(mp.s[y].salt_w, t.h_salt, t.salt_len);
+            const uint8_t one = 0x01;
+            mp.s[y].info_blocks = pad_words(mp.s[y].info_w, t.h_info, t.info_len, &one, 1, 64);
         }
+        const uint64_t per = tiles * mp.count >= kMultiStrideMin * (uint64_t)cu_count() ? 2 : 1;
+        const unsigned gx = (unsigned)((tiles + per - 1) / per);
         hipLaunchKernelGGL(k_derive_multi, dim3(gx, mp.count), dim3(kWG), 0, s, d_rev, n_id, d_key_out,
                            d_mid_out, mp);
         int rc = launch_status("k_derive_multi launch");

@@ -70,12 +70,17 @@ struct GrabCaps {
     uint8_t cap[kBins];
 };
 
-// HKDF parameters shared by all identities of a keyset (kernel argument).
+// HKDF parameters shared by all identities of a keyset (kernel argument), laid
+// out by the host as big-endian message words so that the kernels assemble no
+// bytes: the salt's key block K0 (RFC 2104) or, for a salt longer than the
+// block, its padded message blocks (FIPS 180-4 sec. 5.1.1), and the expand
+// input info || 0x01 padded as it follows the 64-byte key block.
+constexpr uint32_t kMaxSaltBlocks = (kMaxSalt + 9 + 63) / 64;
 struct HkdfParams {
-    uint32_t salt_len;
-    uint32_t info_len;
-    uint8_t salt[kMaxSalt];
-    uint8_t info[kMaxInfo + 1];
+    uint32_t salt_blocks;  // 0: salt_w[0..15] is K0; else padded blocks of a long salt
+    uint32_t info_blocks;
+    uint32_t salt_w[16 * kMaxSaltBlocks];
+    uint32_t info_w[16 * kMaxInfoBlocks];
 };
 
 // Several HKDF parameter sets in one launch (one per grid row): short salts
@@ -83,11 +88,12 @@ struct HkdfParams {
 constexpr uint32_t kMultiStreams = 16;
 constexpr uint32_t kMultiSalt = 64;
 constexpr uint32_t kMultiInfo = 64;
+constexpr uint32_t kMultiInfoBlocks = (kMultiInfo + 1 + 9 + 63) / 64;
 struct StreamParams {
-    uint32_t salt_len;
-    uint32_t info_len;
-    uint8_t salt[kMultiSalt];
-    uint8_t info[kMultiInfo];
+    static constexpr uint32_t salt_blocks = 0;  // at most one block: K0 itself
+    uint32_t info_blocks;
+    uint32_t salt_w[16];
+    uint32_t info_w[16 * kMultiInfoBlocks];
 };
 struct MultiHkdf {
     uint32_t first;  // index of s[0] among the call's streams

@@ -469,7 +469,7 @@ __global__ void __launch_bounds__(kWG) ACE_WAVES(4) k_verify_ordered(Batch bt, K
 {
     __shared__ HkdfPrep prep;
     if constexpr (PER_TX_KEYS) {
-        if (threadIdx.x < 64) hkdf_prepare(hp, prep);
+        hkdf_prepare(hp, prep);
         __syncthreads();
     }
     const Totals T = totals(bt);
@@ -784,7 +784,7 @@ __global__ void __launch_bounds__(kWG) ACE_WAVES(4) k_verify_binned(Batch bt, Ke
     __shared__ HkdfPrep prep;
     __shared__ uint32_t ostart[kBins], ocount[kBins], oend[kBins];
     if constexpr (PER_TX_KEYS) {
-        if (threadIdx.x < 64) hkdf_prepare(hp, prep);
+        hkdf_prepare(hp, prep);
     }
     if (threadIdx.x < kBins) {
         ostart[threadIdx.x] = ctrl->ostart[threadIdx.x];

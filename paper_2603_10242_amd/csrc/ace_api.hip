@@ -190,6 +190,7 @@ struct Plan {
     bool per_tx;
     bool persistent;
     bool rev;
+    uint32_t flags;
     bool attest;  // paper-form records (payload binding + credential over obj_hash || domain)
     uint32_t n_blocks;
     uint64_t total_tx;
@@ -211,6 +212,7 @@ int check_keyset(const ace_keyset *keys, uint32_t flags, Plan &p)
         return fail(ACE_ERR_INVALID_ARG, "ACE_ORDERED and ACE_BUCKETED are exclusive");
     if (keys->kind != ACE_KEYS_MIDSTATE && keys->kind != ACE_KEYS_REV)
         return fail(ACE_ERR_INVALID_ARG, "unknown keyset kind %d", keys->kind);
+    p.flags = flags;
     p.rev = keys->kind == ACE_KEYS_REV;
     p.per_tx = (flags & ACE_PER_TX_KEYS) != 0;
     if (p.per_tx && !p.rev)
@@ -400,22 +402,67 @@ constexpr uint64_t kCountWGs = 256;
 
 // Verify-kernel launches for the plan's key source, persistence and record form.
 template <bool PT, bool AT>
-void launch_ordered_t(unsigned g, hipStream_t s, const Batch &bt, const KeySource &ks,
-                      const HkdfParams &hp)
+void launch_ordered_t(unsigned g, unsigned threads, hipStream_t s, const Batch &bt, const KeySource &ks,
+                      const HkdfParams &hp, bool solo)
 {
-    hipLaunchKernelGGL((k_verify_ordered<PT, AT>), dim3(g), dim3(kWG), 0, s, bt, ks, hp);
+    hipLaunchKernelGGL((k_verify_ordered<PT, AT>), dim3(g), dim3(threads), 0, s, bt, ks, hp,
+                       (uint32_t)solo);
 }
 
-void launch_ordered(const Plan &p, unsigned g, hipStream_t s, const Batch &bt, const KeySource &ks,
-                    const HkdfParams &hp)
+void launch_ordered(bool attest, bool per_tx, unsigned g, unsigned threads, hipStream_t s, const Batch &bt,
+                    const KeySource &ks, const HkdfParams &hp, bool solo)
 {
-    if (p.attest) {
-        if (p.per_tx) launch_ordered_t<true, true>(g, s, bt, ks, hp);
-        else launch_ordered_t<false, true>(g, s, bt, ks, hp);
+    if (attest) {
+        if (per_tx) launch_ordered_t<true, true>(g, threads, s, bt, ks, hp, solo);
+        else launch_ordered_t<false, true>(g, threads, s, bt, ks, hp, solo);
     } else {
-        if (p.per_tx) launch_ordered_t<true, false>(g, s, bt, ks, hp);
-        else launch_ordered_t<false, false>(g, s, bt, ks, hp);
+        if (per_tx) launch_ordered_t<true, false>(g, threads, s, bt, ks, hp, solo);
+        else launch_ordered_t<false, false>(g, threads, s, bt, ks, hp, solo);
     }
+}
+
+template <bool AT>
+void launch_local_t(bool wide, unsigned g, hipStream_t s, const Batch &bt, const KeySource &ks)
+{
+    if (wide) hipLaunchKernelGGL((k_verify_local<AT, 16>), dim3(g), dim3(1024), 0, s, bt, ks);
+    else hipLaunchKernelGGL((k_verify_local<AT, 8>), dim3(g), dim3(512), 0, s, bt, ks);
+}
+
+// The verify form of a call (or, with the maxima's wave tiles, of a graph).
+//   in order      at most one wave per SIMD: the longest message's chain takes
+//                 the whole time, and sorting could not shorten it (2,903
+//                 transactions 82 us; with three more launches and windows
+//                 loaded when needed 128-139).
+//   local         100,000 txs with 50,000 derived keys 73 us against 93 in
+//                 order; 1M txs 248 us against 257 globally binned, 256 blocks
+//                 of 7.66M txs 1,745 against 1,803.
+//   global bins   beyond kLocalMaxWaves wave tiles its fuller waves make up for
+//                 its passes: 16M txs with 1M derived keys 4,000-4,130 us
+//                 against 4,105-4,180 locally sorted.  Persistent waves and
+//                 per-transaction keys, on request, exist in this form only.
+enum Form { kInOrder, kLocal, kGlobalBins };
+constexpr uint64_t kLocalMaxWaves = 1u << 17;
+
+Form form_of(const Plan &p, uint64_t waves, unsigned cus)
+{
+    if (p.mode == kBinned && (p.persistent || p.per_tx)) return kGlobalBins;
+    if ((p.flags & ACE_ORDERED) || p.per_tx) return kInOrder;
+    if (waves > kLocalMaxWaves) return p.mode == kBinned ? kGlobalBins : kLocal;
+    if (p.flags & ACE_BUCKETED) return kLocal;
+    return waves <= 4ull * cus ? kInOrder : kLocal;
+}
+
+// Shape of the local form: up to 64 wave tiles per CU one workgroup of 16
+// waves takes all of a CU's share, sorted together; beyond, two of 8 waves
+// run on a CU at a time, so that one's start and end are filled by the other.
+struct LocalShape {
+    bool wide;
+    uint32_t slots;
+};
+LocalShape local_shape(uint64_t waves, unsigned cus)
+{
+    const bool wide = waves <= 64ull * cus;
+    return LocalShape{wide, wide ? cus : 2 * cus};
 }
 
 template <bool PT, bool PE, bool AT>
@@ -454,19 +501,29 @@ int enqueue_stages(const Plan &p, const Batch &bt, const ace_keyset *keys, const
     const ace_tuning tn = tuning();
     const unsigned cus = (unsigned)cu_count();
     Ctrl *ctrl = reinterpret_cast<Ctrl *>(ws + p.off_ctrl);
-    const bool binned = p.mode == kBinned;
+    // wave tiles: the call's, or the most a replay can have
+    const uint64_t waves = graph ? (p.total_tx + 63) / 64 + p.n_blocks : p.total_waves;
+    const Form form = form_of(p, waves, cus);
+    const bool binned = form == kGlobalBins;
 
     KeySource ks;
     ks.n_id = keys->n_id;
     ks.mid = nullptr;
     ks.rev = nullptr;
-    // keys derived in the call: in the binned form the derivation (VALU-bound)
-    // runs on a second stream beside the binning passes (memory-bound), which
-    // do not depend on it; the verify kernel waits for both
+    // Keys derived in the call.  In-order calls without a flag have at most one
+    // wave per SIMD: each lane derives its own transaction's key, which costs
+    // idle lanes and saves a launch and the midstates' way through memory.
+    // In the binned form the derivation (VALU-bound) runs on a second stream
+    // beside the binning passes (memory-bound), which do not depend on it; the
+    // verify kernel waits for both.
+    const bool per_tx = p.per_tx || (p.rev && form == kInOrder && !(p.flags & ACE_ORDERED));
+    unsigned long long *const zero = graph || p.n_blocks > 1 ? nullptr : bt.one.count;  // else cleared already
+    const bool solo = zero && form == kInOrder && p.total_waves <= kWavesPerWG && p.total_tx;
+    bool cleared = !zero || solo;
     Fork *fk = nullptr;
     if (!p.rev) {
         ks.mid = keys->d_mid;
-    } else if (p.per_tx) {
+    } else if (per_tx) {
         ks.rev = keys->d_rev;
     } else {
         uint32_t *mid = reinterpret_cast<uint32_t *>(ws + p.off_mid);
@@ -483,8 +540,9 @@ int enqueue_stages(const Plan &p, const Batch &bt, const ace_keyset *keys, const
                 if (tn.derive_wgs_per_cu) g = std::min<unsigned>(g, tn.derive_wgs_per_cu * cus);
             }
             hipLaunchKernelGGL(k_derive, dim3(g), dim3(kWG), 0, ds, keys->d_rev, keys->n_id,
-                               (uint8_t *)nullptr, mid, hp);
+                               (uint8_t *)nullptr, mid, hp, binned ? (unsigned long long *)nullptr : zero);
             if ((rc = launch_status("k_derive launch"))) return rc;
+            if (!binned) cleared = true;
             if (fk) {
                 if ((rc = check_hip(hipEventRecord(fk->join, fk->aux), "hipEventRecord"))) return rc;
                 // A timing-enabled marker on the caller's stream right after the
@@ -498,7 +556,7 @@ int enqueue_stages(const Plan &p, const Batch &bt, const ace_keyset *keys, const
     }
     prof_mark(prof, 1, s);
 
-    if (!graph) {
+    if (!graph && (binned || !cleared)) {
         hipLaunchKernelGGL(k_zero, dim3(grid_for(p.n_blocks, kWG, 1024)), dim3(kWG), 0, s, bt,
                            binned ? ctrl : (Ctrl *)nullptr);
         if ((rc = launch_status("k_zero launch"))) return rc;
@@ -506,19 +564,22 @@ int enqueue_stages(const Plan &p, const Batch &bt, const ace_keyset *keys, const
 
     if (!binned) {
         prof_mark(prof, 2, s);
-        if (graph || p.total_tx) {
-            const unsigned g = graph ? tn.verify_wgs_per_cu * cus
-                                     : grid_for(p.total_waves, kWavesPerWG, 0x7fffffffu);
-            launch_ordered(p, g, s, bt, ks, hp);
+        if ((graph || p.total_tx) && form == kInOrder) {
+            // workgroups of one wave, spread over the CUs; of four where they
+            // share a parameter set's preparation or the whole call
+            const unsigned wpw = per_tx || solo ? kWavesPerWG : 1;
+            unsigned g = grid_for(waves, wpw, 0x7fffffffu);
+            if (graph) g = std::min<unsigned>(g, tn.verify_wgs_per_cu * cus * (kWavesPerWG / wpw));
+            launch_ordered(p.attest, per_tx, g, 64 * wpw, s, bt, ks, hp, solo);
             if ((rc = launch_status("k_verify_ordered launch"))) return rc;
+        } else if (graph || p.total_tx) {
+            const LocalShape sh = local_shape(waves, cus);
+            const unsigned g = local_share(waves, sh.slots).groups;
+            if (p.attest) launch_local_t<true>(sh.wide, g, s, bt, ks);
+            else launch_local_t<false>(sh.wide, g, s, bt, ks);
+            if ((rc = launch_status("k_verify_local launch"))) return rc;
         }
         prof_mark(prof, 3, s);
-        if (graph || p.total_tx) {
-            hipLaunchKernelGGL(k_count, dim3(grid_for(graph ? (p.total_tx + kTile - 1) / kTile + p.n_blocks
-                                                            : p.total_tiles, 1, kCountWGs)),
-                               dim3(kWG), 0, s, bt);
-            if ((rc = launch_status("k_count launch"))) return rc;
-        }
         prof_mark(prof, 4, s);
         return ACE_OK;
     }
@@ -681,7 +742,8 @@ ACE_API int ace_derive_keys(const uint8_t *d_rev, uint32_t n_id, const uint8_t *
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const unsigned grid = std::min<unsigned>((unsigned)((n_id + kWG - 1) / kWG),
                                              kDeriveWgsPerCu * (unsigned)cu_count());
-    hipLaunchKernelGGL(k_derive, dim3(grid), dim3(kWG), 0, s, d_rev, n_id, d_key_out, d_mid_out, hp);
+    hipLaunchKernelGGL(k_derive, dim3(grid), dim3(kWG), 0, s, d_rev, n_id, d_key_out, d_mid_out, hp,
+                       (unsigned long long *)nullptr);
     return launch_status("k_derive launch");
 }
 
@@ -902,6 +964,8 @@ int run_plan(const Plan &p, const ace_keyset *keys, const ace_block *blocks, uin
     bt.total_tx = p.total_tx;
     bt.total_tiles = p.total_tiles;
     bt.total_waves = p.total_waves;
+    const unsigned cus = (unsigned)cu_count();
+    bt.share = local_share(p.total_waves, local_shape(p.total_waves, cus).slots);
     DescChunk chunk;
     memset(&chunk, 0, sizeof chunk);
     uint64_t tx0 = 0, tile0 = 0, wave0 = 0;
@@ -1135,7 +1199,8 @@ ACE_API int ace_graph_create(const ace_keyset *keys, uint32_t max_blocks, uint64
             return rc;
         }
         hipLaunchKernelGGL(k_plan, dim3(1), dim3(kPlanWG), 0, g->capture, d_descs, d_n,
-                           max_blocks, table, hdr, p.mode == kBinned ? ctrl : (Ctrl *)nullptr);
+                           max_blocks, table, hdr, p.mode == kBinned ? ctrl : (Ctrl *)nullptr,
+                           local_shape((max_tx + 63) / 64 + max_blocks, (unsigned)cu_count()).slots);
         rc = launch_status("k_plan launch");
         if (!rc) rc = enqueue_stages(p, bt, keys, hp, ws, g->capture, nullptr, true);
         hipGraph_t graph = nullptr;

@@ -29,6 +29,29 @@ struct DevBlock {
     uint64_t wave0;  // first wave tile of the in-order verify (64 per wave)
 };
 
+// How the local verify form shares a call's wave tiles among its workgroups:
+// workgroup g takes base of them, one more if g < extra.
+struct LocalShare {
+    uint32_t groups;
+    uint32_t base;
+    uint32_t extra;
+};
+constexpr uint32_t kLocalUnits = 64;  // most wave tiles per workgroup: 4,096 transactions
+
+// `slots`: workgroups that run at once.  As many rounds of them as the wave
+// tiles need, every workgroup with the same share, so that the last round is
+// as full as the first.
+__host__ __device__ inline LocalShare local_share(uint64_t waves, uint32_t slots)
+{
+    const uint32_t w = (uint32_t)waves;  // at most 2^26 of 64 transactions and 2^24 part-filled ones
+    const uint32_t rounds = (w + slots * kLocalUnits - 1) / (slots * kLocalUnits);
+    LocalShare s;
+    s.groups = slots * (rounds ? rounds : 1u);
+    s.base = w / s.groups;
+    s.extra = w - s.base * s.groups;
+    return s;
+}
+
 // Sizes of a call that a captured graph reads from device memory (they
 // change from replay to replay while the kernel arguments stay fixed).
 struct BatchHdr {
@@ -37,6 +60,7 @@ struct BatchHdr {
     uint64_t total_tx;
     uint64_t total_tiles;
     uint64_t total_waves;
+    LocalShare share;
 };
 
 // Blocks of one call: a single block travels inline in the kernel arguments,
@@ -50,6 +74,7 @@ struct Batch {
     uint64_t total_tx;
     uint64_t total_tiles;
     uint64_t total_waves;
+    LocalShare share;
 };
 
 // Control words of a bucketed pass (start of the workspace).  The per-tile

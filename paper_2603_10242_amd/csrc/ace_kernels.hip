@@ -4,7 +4,8 @@
 //   k_bin_count      histogram of transactions by inner block count.
 //   k_bin_scan       bin start positions, longest messages first.
 //   k_bin_scatter    transaction records into bin order.
-//   k_verify         Alg. 1 Phase 1a per transaction: inner hash of the message
+//   k_verify_*       Alg. 1 Phase 1a per transaction (in input order, sorted
+//                    by block count within a workgroup, or binned globally): inner hash of the message
 //                    from the cached ipad midstate, outer hash from the opad
 //                    midstate, constant-time compare with the credential,
 //                    wave64 ballot of the verdicts (also the paper's
@@ -37,6 +38,7 @@ struct U4 {
 // so waiting for the round constants' scalar loads does not also wait for
 // them.
 typedef const __attribute__((address_space(1))) uint32_t *gptr;
+typedef const __attribute__((address_space(1))) uint64_t *gptr64;
 __device__ __forceinline__ U4 load16(const uint32_t *p)
 {
     const gptr g = (gptr)p;
@@ -52,6 +54,7 @@ struct Totals {
     uint32_t n_blocks;
     bool inline_one;
     uint64_t tx, tiles, waves;
+    LocalShare share;
 };
 
 // The same value in every lane, made visible to the compiler as such, so
@@ -71,12 +74,16 @@ __device__ __forceinline__ Totals totals(const Batch &bt)
         t.tx = uniform64(bt.hdr->total_tx);
         t.tiles = uniform64(bt.hdr->total_tiles);
         t.waves = uniform64(bt.hdr->total_waves);
+        t.share.groups = uniform32(bt.hdr->share.groups);
+        t.share.base = uniform32(bt.hdr->share.base);
+        t.share.extra = uniform32(bt.hdr->share.extra);
         t.inline_one = false;
     } else {
         t.n_blocks = bt.n_blocks;
         t.tx = bt.total_tx;
         t.tiles = bt.total_tiles;
         t.waves = bt.total_waves;
+        t.share = bt.share;
         t.inline_one = bt.n_blocks == 1;
     }
     return t;
@@ -214,6 +221,36 @@ __device__ __forceinline__ void window_words(uint32_t (&W)[16], const uint32_t (
     for (int j = 0; j < 16; ++j) W[j] = __builtin_amdgcn_perm(D[16 * S + j + 1], D[16 * S + j], sel);
 }
 
+// SHA-256 padding of block b (words W, rb message bytes from its start on):
+// word jf holds byte rb (the 0x80 marker) after its c message bytes; earlier
+// words are message, later ones zero.  In the last block the marker is in words
+// 0..13 (or was in the block before: jf < 0) and words 14..15 hold the bit
+// length; in a block before it, the message fills 56..63 bytes, so only words
+// 14..15 change.
+__device__ __forceinline__ void pad_block(uint32_t (&W)[16], const LaneGeom &g, int64_t rb, uint32_t b)
+{
+    const int32_t r0 = (int32_t)rb;
+    const int32_t jf = r0 >> 2;  // negative: the marker was in the previous block
+    const uint32_t c8 = ((uint32_t)r0 & 3u) << 3;
+    const uint32_t keep = ~(0xFFFFFFFFu >> c8);
+    const uint32_t pad = 0x80000000u >> c8;
+    if (b + 1 == g.nb) {
+#pragma unroll
+        for (int j = 0; j < 14; ++j) {
+            const uint32_t part = (W[j] & keep) | pad;
+            W[j] = j < jf ? W[j] : (j == jf ? part : 0u);
+        }
+        W[14] = g.len_hi;
+        W[15] = g.len_lo;
+    } else {
+#pragma unroll
+        for (int j = 14; j < 16; ++j) {
+            const uint32_t part = (W[j] & keep) | pad;
+            W[j] = j < jf ? W[j] : (j == jf ? part : 0u);
+        }
+    }
+}
+
 // The message blocks of one lane, chained onto S.  The windows of up to K
 // consecutive blocks come in one load of 16 K + 1 dwords (K blocks touch
 // about 1 + (64 K + 3) / 128 cache lines together instead of about 1.5 each),
@@ -283,39 +320,38 @@ __device__ __forceinline__ void message_blocks(State &S, bool live, bool overrea
             else window_words<K - 1, K>(W, D, g.sel);
             ++slot;
             --avail;
-            if (rb < 64) {
-                // padding: word jf holds byte rb (the 0x80 marker) after its c
-                // message bytes; earlier words are message, later ones zero.
-                // In the last block the marker is in words 0..13 (or was in the
-                // block before: jf < 0) and words 14..15 hold the bit length;
-                // in a block before it, the message fills 56..63 bytes, so only
-                // words 14..15 change.  (Lanes of a binned wave share their
-                // block count, so one of the two branches runs per block.)
-                const int32_t r0 = (int32_t)rb;
-                const int32_t jf = r0 >> 2;   // negative: the marker was in the previous block
-                const uint32_t c8 = ((uint32_t)r0 & 3u) << 3;
-                const uint32_t keep = ~(0xFFFFFFFFu >> c8);
-                const uint32_t pad = 0x80000000u >> c8;
-                if (b + 1 == g.nb) {
-#pragma unroll
-                    for (int j = 0; j < 14; ++j) {
-                        const uint32_t part = (W[j] & keep) | pad;
-                        W[j] = j < jf ? W[j] : (j == jf ? part : 0u);
-                    }
-                    W[14] = g.len_hi;
-                    W[15] = g.len_lo;
-                } else {
-#pragma unroll
-                    for (int j = 14; j < 16; ++j) {
-                        const uint32_t part = (W[j] & keep) | pad;
-                        W[j] = j < jf ? W[j] : (j == jf ? part : 0u);
-                    }
-                }
-            }
+            if (rb < 64) pad_block(W, g, rb, b);
             compress_block(S, W);
         }
         ++b; q += 16; rb -= 64;
         run = live && b < g.nb;
+    } while (__ballot(run) != 0);
+}
+
+// The same for a wave that has its SIMD to itself (a small call): nothing
+// else hides a load's latency, so block b + 1's window is loaded while block b
+// is compressed.
+__device__ __forceinline__ void message_blocks_ahead(State &S, bool live, bool overread_ok,
+                                                     const LaneGeom &g, int64_t L)
+{
+    const uint32_t *q = g.A0;
+    int64_t rb = L;
+    uint32_t b = 0;
+    bool run = live;
+    uint32_t D[17];
+    if (run) load_window(D, q, rb, overread_ok, g.A0, g.last, 0);
+    if (__ballot(run)) do {
+        uint32_t W[16];
+        window_words<0, 1>(W, D, g.sel);
+        q += 16;
+        const bool next = run && b + 1 < g.nb;
+        if (next) load_window(D, q, rb - 64, overread_ok, g.A0, g.last, b + 1);
+        if (run) {
+            if (rb < 64) pad_block(W, g, rb, b);
+            compress_block(S, W);
+        }
+        ++b; rb -= 64;
+        run = next;
     } while (__ballot(run) != 0);
 }
 
@@ -402,12 +438,18 @@ __device__ __forceinline__ void load_midstates(const uint32_t *mid, uint32_t (&M
 // HMAC form: valid iff HMAC(k, msg) == credential.
 // Paper form (ATTEST): the message is the payload P; valid iff SHA-256(P) ==
 // obj_hash (payload binding) and HMAC(k, obj_hash || domain) == credential.
-template <bool PER_TX_KEYS, bool ATTEST, bool FOLD>
+// AHEAD: for a wave that has its SIMD to itself: every load goes out as early
+// as it can.
+template <bool PER_TX_KEYS, bool ATTEST, bool FOLD, bool AHEAD = false>
 __device__ __forceinline__ bool verify_lane(bool live, const TxRef &t, const HkdfPrep *prep)
 {
     State ipad, opad;
 #pragma unroll
     for (int i = 0; i < 8; ++i) { ipad.h[i] = 0; opad.h[i] = 0; }
+    uint32_t C[check_words<ATTEST>()];
+#pragma unroll
+    for (int i = 0; i < check_words<ATTEST>(); ++i) C[i] = 0;
+    if (AHEAD && live) load_check<ATTEST>(t.tag, C);
     if constexpr (PER_TX_KEYS) {
         uint32_t rv[8];
         if (live) {
@@ -421,25 +463,28 @@ __device__ __forceinline__ bool verify_lane(bool live, const TxRef &t, const Hkd
         }
         uint32_t key[8];
         derive_lane(live, rv, *prep, key, ipad, opad);
-    } else {
-        if (live) {
-            uint32_t M[16];
-            load_midstates(t.mid, M);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) { ipad.h[i] = M[i]; opad.h[i] = M[8 + i]; }
-        }
     }
+    // The paper form's payload digest needs no key: its midstates are loaded
+    // after it (sixteen registers fewer during the message blocks).
+    constexpr bool kMidLater = ATTEST && !AHEAD;
+    auto midstates = [&] {
+        if (PER_TX_KEYS || !live) return;
+        uint32_t M[16];
+        load_midstates(t.mid, M);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) { ipad.h[i] = M[i]; opad.h[i] = M[8 + i]; }
+    };
+    if constexpr (!kMidLater) midstates();
     // the message chain starts from the ipad state (HMAC inner hash) or, for
     // the payload digest, from the initial value
     State S = ATTEST ? initial_state() : ipad;
     const LaneGeom g = lane_geom<ATTEST>(live, t);
     // three windows per load where the registers allow it; the per-transaction
     // derivation's state leaves room for two
-    message_blocks<PER_TX_KEYS ? 2 : 3>(S, live, t.overread_ok, g, (int64_t)t.L);
-    uint32_t C[check_words<ATTEST>()];
-#pragma unroll
-    for (int i = 0; i < check_words<ATTEST>(); ++i) C[i] = 0;
-    if (live) load_check<ATTEST>(t.tag, C);
+    if constexpr (AHEAD) message_blocks_ahead(S, live, t.overread_ok, g, (int64_t)t.L);
+    else message_blocks<PER_TX_KEYS ? 2 : 3>(S, live, t.overread_ok, g, (int64_t)t.L);
+    if constexpr (kMidLater) midstates();
+    if (!AHEAD && live) load_check<ATTEST>(t.tag, C);
     return lane_result<ATTEST, FOLD>(live, S, ipad, opad, C);
 }
 
@@ -462,12 +507,20 @@ __device__ __forceinline__ bool load_tx(const DevBlock &d, uint64_t i, const Key
 
 // ------------------------------------------------------------------------------------------
 // k_verify, in-order form: wave tile w covers transactions 64w' .. 64w'+63 of
-// one block; the ballot is that block's two bitmask words.
+// one block; the ballot is that block's two bitmask words, its population
+// count goes to the block's count (cleared before).  `solo`: the whole call is
+// one workgroup, which stores the count itself (nothing needs to clear it).
+//
+// Bound by one wave's chain of compressions: it serves calls of at most one
+// wave per SIMD (and ACE_ORDERED), where a lone wave issues a VALU instruction
+// every 4.3 cycles, so whatever it waits for besides costs the call its time.
 // ------------------------------------------------------------------------------------------
 template <bool PER_TX_KEYS, bool ATTEST>
-__global__ void __launch_bounds__(kWG) ACE_WAVES(4) k_verify_ordered(Batch bt, KeySource ks, HkdfParams hp)
+__global__ void __launch_bounds__(kWG) ACE_WAVES(4) k_verify_ordered(Batch bt, KeySource ks, HkdfParams hp,
+                                                                     uint32_t solo)
 {
     __shared__ HkdfPrep prep;
+    __shared__ uint32_t part[kWavesPerWG];
     if constexpr (PER_TX_KEYS) {
         hkdf_prepare(hp, prep);
         __syncthreads();
@@ -475,8 +528,9 @@ __global__ void __launch_bounds__(kWG) ACE_WAVES(4) k_verify_ordered(Batch bt, K
     const Totals T = totals(bt);
     // grid-stride over wave tiles (wave-uniform loop bound)
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    for (uint64_t w = (uint64_t)blockIdx.x * kWavesPerWG + wave; w < T.waves;
-         w += (uint64_t)gridDim.x * kWavesPerWG) {
+    const uint32_t wpw = blockDim.x >> 6;
+    uint32_t found = 0;  // solo: valid transactions of this wave
+    for (uint64_t w = (uint64_t)blockIdx.x * wpw + wave; w < T.waves; w += (uint64_t)gridDim.x * wpw) {
         const uint32_t b = find_block<1>(bt, T, w);
         const DevBlock d = get_block(bt, T, b);
         const uint64_t i0 = 64ull * (w - d.wave0);
@@ -485,11 +539,196 @@ __global__ void __launch_bounds__(kWG) ACE_WAVES(4) k_verify_ordered(Batch bt, K
         TxRef t{};
         bool live = false;
         if (active) live = load_tx<ATTEST>(d, i, ks, t);
-        const bool valid = verify_lane<PER_TX_KEYS, ATTEST, !ATTEST>(live, t, &prep) && live;
+        const bool valid = verify_lane<PER_TX_KEYS, ATTEST, !ATTEST, true>(live, t, &prep) && live;
         const unsigned long long m = __ballot(valid);
         if (lane_id() == 0) {
             d.bitmask[i0 >> 5] = (uint32_t)m;
             if (i0 + 32 < d.n) d.bitmask[(i0 >> 5) + 1] = (uint32_t)(m >> 32);
+            if (!solo && m) atomicAdd(d.count, (unsigned long long)__popcll(m));
+        }
+        found = (uint32_t)__popcll(m);
+    }
+    if (solo) {
+        if (lane_id() == 0) part[wave] = found;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t s = 0;
+            for (uint32_t k = 0; k < wpw; ++k) s += part[k];
+            *bt.one.count = s;
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// k_verify, local form: a workgroup takes a run of wave tiles (64 transactions
+// of one block each, in input order, over all blocks of the call), sorts their
+// transactions by block count in LDS, longest first, and its waves take 64 of
+// them at a time, so that a wave's lanes finish together; verdict bits return
+// to input order in LDS, from where they go to the bitmasks and counts.
+//
+// Bound by VALU issue.  One launch takes the place of the six passes around
+// the globally binned verify (count, scan, scatter, finalize, count and their
+// 56 bytes per transaction; 39 us of 257 for 1M transactions).  What it gives
+// up: sorting 4,096 transactions fills 97.7% of the sweep's lanes instead of
+// 99.9% (2,048: 95.3%), and a CU's share is fixed.  8,192 per workgroup measured
+// slower (16M transactions +4%: the messages in flight spread over twice the
+// memory), 2,048 no faster.
+// ------------------------------------------------------------------------------------------
+// Waves of one SIMD at four priorities, the first tiles' (the longest) highest.
+// At equal ones they go through their tiles in step and wait for memory
+// together: 256 blocks of 7.66M transactions 1,776 -> 1,730 us, 16M transactions
+// 4,146 -> 4,065 us (locally sorted, one box); in the opposite order the longest
+// tiles end last (1M transactions +5%), and priorities taking turns per block
+// gained nothing.
+__device__ __forceinline__ void set_row_priority(uint32_t row)
+{
+    if (row == 0) __builtin_amdgcn_s_setprio(3);
+    else if (row == 1) __builtin_amdgcn_s_setprio(2);
+    else if (row == 2) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+}
+
+template <bool ATTEST, int NW>
+__global__ void __launch_bounds__(64 * NW) ACE_WAVES(4) k_verify_local(Batch bt, KeySource ks)
+{
+    // what a lane needs to find transaction l of a wave tile
+    struct Unit {
+        const uint64_t *off;
+        const uint32_t *id;
+        const uint8_t *msg, *tag;
+        uint64_t area_end;
+        uint32_t n, block;  // transactions in the tile, its block
+        uint64_t i0;        // its first transaction within the block
+    };
+    constexpr int kPerThread = kLocalUnits / NW;
+    __shared__ Unit unit[kLocalUnits];
+    __shared__ uint16_t order[64 * kLocalUnits];
+    __shared__ uint32_t mask[2 * kLocalUnits];
+    __shared__ uint32_t hist[kBins], start[kBins];
+    __shared__ uint32_t n_live, next_tile;
+
+    const Totals T = totals(bt);
+    const LocalShare sh = T.share;
+    // until the tiles are sorted nothing of this workgroup can run (beside
+    // another workgroup's compressions at equal priority the sort took 79 us
+    // instead of 12)
+    __builtin_amdgcn_s_setprio(3);
+    if (blockIdx.x >= sh.groups) return;  // the whole workgroup
+    const uint32_t U = sh.base + (blockIdx.x < sh.extra ? 1u : 0u);  // <= kLocalUnits
+    const uint32_t u0 = blockIdx.x * sh.base + (blockIdx.x < sh.extra ? blockIdx.x : sh.extra);
+    const uint32_t tid = threadIdx.x;
+    const uint32_t lane = lane_id();
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid < 2 * kLocalUnits) mask[tid] = 0;
+    if (tid < kBins) hist[tid] = 0;
+    if (tid == 0) next_tile = NW;
+    if (tid < U) {
+        const uint32_t w = u0 + tid;
+        const uint32_t b = find_block<1>(bt, T, w);
+        const DevBlock d = get_block(bt, T, b);
+        const uint64_t i0 = 64ull * (w - d.wave0);
+        Unit x;
+        x.off = d.off + i0;
+        x.id = d.id + i0;
+        x.msg = d.msg;
+        x.tag = d.tag + (uint64_t)check_stride<ATTEST>() * i0;
+        x.area_end = d.off[d.n];
+        x.n = d.n - i0 < 64 ? (uint32_t)(d.n - i0) : 64u;
+        x.block = b;
+        x.i0 = i0;
+        unit[tid] = x;
+    }
+    __syncthreads();
+
+    // block counts and ranks: wave w takes tiles w, w + NW, ...
+    uint32_t bin[kPerThread], rank[kPerThread];
+#pragma unroll
+    for (int k = 0; k < kPerThread; ++k) {
+        bin[k] = kBins;
+        const uint32_t u = wave + k * NW;
+        if (u < U && lane < unit[u].n) {
+            const gptr64 off = (gptr64)unit[u].off;
+            const uint64_t a = off[lane], e = off[lane + 1];
+            const uint32_t who = ((gptr)unit[u].id)[lane];
+            // those that cannot be valid are left out: their bits stay 0
+            if (a <= e && who < ks.n_id) bin[k] = bin_of_length(e - a);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kPerThread; ++k)
+        if (bin[k] < kBins) rank[k] = atomicAdd(&hist[bin[k]], 1u);
+    __syncthreads();
+    if (wave == 0) {
+        // start of every bin, longest first (lane l: bin 63 - l)
+        const uint32_t c = hist[kBins - 1 - lane];
+        uint32_t s = c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t v = __shfl_up(s, d);
+            if ((int)lane >= d) s += v;
+        }
+        start[kBins - 1 - lane] = s - c;
+        if (lane == 63) n_live = s;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kPerThread; ++k)
+        if (bin[k] < kBins) order[start[bin[k]] + rank[k]] = (uint16_t)(64u * (wave + k * NW) + lane);
+    __syncthreads();
+
+    // Tiles of 64 in sorted order.  The first NW go to the waves so that each
+    // SIMD's share is even when there are few (waves w and w + 4 share a SIMD:
+    // every second row of four in reverse); the others are taken one by one.
+    const uint32_t live_n = n_live;
+    set_row_priority(wave >> 2);
+    const uint32_t tiles = (live_n + 63) >> 6;
+    uint32_t tile = (wave & 4u) ? (wave & ~3u) + 3u - (wave & 3u) : wave;
+    while (tile < tiles) {
+        // the last tiles at equal priority: the low rows would be left with theirs
+        if (tile + 2 * NW >= tiles) __builtin_amdgcn_s_setprio(0);
+        const uint32_t p = 64 * tile + lane;
+        const bool live = p < live_n;
+        uint32_t x = 0;
+        TxRef t{};
+        if (live) {
+            x = order[p];
+            const Unit &un = unit[x >> 6];
+            const uint32_t l = x & 63u;
+            const uint64_t a = ((gptr64)un.off)[l], e = ((gptr64)un.off)[l + 1];
+            const uint32_t who = ((gptr)un.id)[l];
+            t.msg = un.msg + a;
+            t.L = e - a;
+            t.mid = ks.mid + 16ull * who;
+            t.tag = un.tag + check_stride<ATTEST>() * l;
+            t.overread_ok = e + kOverread <= un.area_end;
+        }
+        if (verify_lane<false, ATTEST, true>(live, t, nullptr)) atomicOr(&mask[x >> 5], 1u << (x & 31u));
+        // every lane takes part in the atomic, so that no divergent branch
+        // precedes the readfirstlane
+        tile = __builtin_amdgcn_readfirstlane(atomicAdd(&next_tile, lane == 0 ? 1u : 0u));
+    }
+    __syncthreads();
+    static_assert(kLocalUnits <= 64, "one wave writes the results");
+    if (wave == 0) {
+        // lane u: tile u's bitmask words, then its count, added up per block
+        uint32_t b = 0, c = 0;
+        if (lane < U) {
+            const Unit &x = unit[lane];
+            b = x.block;
+            const uint32_t lo = mask[2 * lane], hi = mask[2 * lane + 1];
+            uint32_t *out = get_block(bt, T, b).bitmask + (x.i0 >> 5);
+            out[0] = lo;
+            if (x.n > 32) out[1] = hi;
+            c = __popc(lo) + __popc(hi);
+        }
+        for (uint32_t at = 0; at < U;) {  // a block's tiles are consecutive lanes
+            const uint32_t b0 = __shfl(b, at);
+            const bool mine = lane < U && b == b0;
+            uint32_t s = mine ? c : 0u;
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d);
+            if (lane == at && s) atomicAdd(get_block(bt, T, b0).count, (unsigned long long)s);
+            at += __popcll(__ballot(mine));
         }
     }
 }
@@ -528,10 +767,7 @@ struct TileTx {
 // Every lane loads (past the block's last transaction it reloads that one,
 // which the caller then ignores): with loads under a branch the compiler
 // waited for all of them, the next tile's included, before using any.
-// (Global, not flat, loads: they count only against the vector memory
-// counter, so LDS accesses do not wait for them.)
-typedef const __attribute__((address_space(1))) uint64_t *gptr64;
-
+// (Global, not flat, loads: LDS accesses do not wait for them.)
 __device__ __forceinline__ void load_tile_tx(const DevBlock &d, uint64_t i0, TileTx &x)
 {
     const gptr64 off = (gptr64)d.off;
@@ -947,7 +1183,8 @@ constexpr int kPlanWG = 1024;
 __global__ void __launch_bounds__(kPlanWG) k_plan(const DevBlock *__restrict__ src,
                                                   const uint32_t *__restrict__ src_n,
                                                   uint32_t max_blocks, DevBlock *__restrict__ table,
-                                                  BatchHdr *__restrict__ hdr, Ctrl *__restrict__ ctrl)
+                                                  BatchHdr *__restrict__ hdr, Ctrl *__restrict__ ctrl,
+                                                  uint32_t slots)
 {
     __shared__ uint64_t sc[3][kPlanWG];
     __shared__ uint64_t carry[3];
@@ -1001,20 +1238,31 @@ __global__ void __launch_bounds__(kPlanWG) k_plan(const DevBlock *__restrict__ s
         hdr->total_tx = carry[0];
         hdr->total_tiles = carry[1];
         hdr->total_waves = carry[2];
+        hdr->share = local_share(carry[2], slots);
     }
 }
 
-// Writes a chunk of block descriptors (passed by value) into the device table.
+// Writes a chunk of block descriptors (passed by value) into the device table
+// and clears their counts.
 __global__ void k_put_descs(DevBlock *table, DescChunk c)
 {
     const uint32_t t = threadIdx.x;
-    if (t < c.count) table[c.first + t] = c.d[t];
+    if (t >= c.count) return;
+    table[c.first + t] = c.d[t];
+    *c.d[t].count = 0;
 }
 
 // Explicit instantiations used by the host entry points.
-template __global__ void k_verify_ordered<false, false>(Batch, KeySource, HkdfParams);
-template __global__ void k_verify_ordered<true, false>(Batch, KeySource, HkdfParams);
-template __global__ void k_verify_ordered<false, true>(Batch, KeySource, HkdfParams);
+template __global__ void k_verify_ordered<false, false>(Batch, KeySource, HkdfParams, uint32_t);
+template __global__ void k_verify_ordered<true, false>(Batch, KeySource, HkdfParams, uint32_t);
+template __global__ void k_verify_ordered<false, true>(Batch, KeySource, HkdfParams, uint32_t);
+template __global__ void k_verify_ordered<true, true>(Batch, KeySource, HkdfParams, uint32_t);
+#define ACE_LOCAL(R, N) template __global__ void k_verify_local<R, N>(Batch, KeySource);
+ACE_LOCAL(false, 8)
+ACE_LOCAL(true, 8)
+ACE_LOCAL(false, 16)
+ACE_LOCAL(true, 16)
+#undef ACE_LOCAL
 #define ACE_BINNED(P, Q, R)                                                                     \
     template __global__ void k_verify_binned<P, Q, R>(Batch, KeySource, HkdfParams, Ctrl *,   \
                                                       const unsigned long long *, const TxRec *, \

@@ -199,10 +199,13 @@ __device__ __forceinline__ void derive_store(bool live, const RevRaw &x, uint64_
     }
 }
 
+// Also clears `zero` (the count of a single-block verify call, or NULL).
 __global__ void __launch_bounds__(kWG) ACE_WAVES(5) k_derive(const uint8_t *__restrict__ rev, uint32_t n_id,
                                                 uint8_t *__restrict__ key_out,
-                                                uint32_t *__restrict__ mid_out, HkdfParams hp)
+                                                uint32_t *__restrict__ mid_out, HkdfParams hp,
+                                                unsigned long long *zero)
 {
+    if (zero && blockIdx.x == 0 && threadIdx.x == 0) *zero = 0;
     // grid-stride: a grid smaller than n_id / kWG leaves CU slots to kernels
     // running beside it on another stream.  Each lane's next identity is
     // loaded before the current one is derived (the first one before the

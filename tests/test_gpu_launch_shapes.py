@@ -37,3 +37,81 @@ def test_derive_multi_tiles_per_workgroup(ace, n_id, n_streams):
     for k, (salt, info) in enumerate(streams):
         want = oracle.hmac_midstates(oracle.derive_keys(rev[pick], salt, info, 8))
         assert np.array_equal(got[k], np.asarray(want).reshape(-1, 16)), k
+
+
+def attestations(n, n_id, n_blocks, seed):
+    w = W.paper_attestations(n=n, n_id=n_id, seed=seed, lengths=lambda r, k: r.integers(0, 400, size=k))
+    return w, w.payload, w.poff, w.att, w.domain
+
+
+def sweep(n, n_id, n_blocks, seed):
+    w = W.generate("shape", seed, n=n, n_id=n_id, lengths=W.lognormal_lengths, p_invalid=0.02,
+                   kinds=(W.KIND_TAG, W.KIND_MSG, W.KIND_KEY))
+    return w, w.msg, w.off, w.tags, w.salt
+
+
+# wave tiles on a 256-CU device: one workgroup (up to 4), one wave per SIMD (1,024), one workgroup
+# per CU (16,384), two per CU and more
+@pytest.mark.parametrize("n,n_blocks", [(1, 1), (64, 1), (65, 1), (256, 1), (257, 1), (700, 9), (65_536, 1),
+                                        (65_537, 1), (66_000, 300), (131_071, 1), (1_048_576, 1),
+                                        (1_048_640, 1), (1_050_000, 41)])
+@pytest.mark.parametrize("form", ["hmac", "attest"])
+def test_open_calls_at_shape_edges(ace, n, n_blocks, form):
+    """Open calls with resident and derived keys, as one block or many uneven
+    ones (empty ones among them), some offsets decreasing and identities
+    unregistered; every bitmask word and count."""
+    import torch
+    attest = form == "attest"
+    n_id = max(2, min(n // 3, 20_000))
+    w, msg, off, tags, salt = (attestations if attest else sweep)(n, n_id, n_blocks, n + 7)
+    ids = w.ids.copy()
+    ids[5::1009] = n_id + 3
+    r = np.random.default_rng(n)
+    cuts = np.sort(np.concatenate([[0, n], r.integers(0, n + 1, n_blocks - 1)]))
+    if n_blocks > 3:
+        cuts[2] = cuts[1]
+    print("%s n=%d blocks=%d" % (form, n, n_blocks), flush=True)
+    d_msg, rev = ace.to_device(msg if msg.size else np.zeros(4, np.uint8)), ace.to_device(w.rev)
+    blocks, want = [], []
+    for a, b in zip(cuts[:-1], cuts[1:]):
+        o = off[a:b + 1].copy()
+        if b - a > 200:
+            o[100] = o[101] + 1     # decreasing: transaction 100 cannot be valid, 99 reads past its end
+        blk = ace.upload_block(None, o, ids[a:b], tags[a:b], msg_dev=d_msg, record_bytes=72 if attest else 32)
+        want.append((oracle.verify_attest if attest else oracle.verify_batch)(w.keys, msg, o, ids[a:b],
+                                                                              tags[a:b], 8))
+        blocks.append(blk)
+    for ks in (ace.midstate_keyset(rev, salt, w.info), ace.rev_keyset(rev, salt, w.info)):
+        for blk in blocks:
+            blk.bitmask.fill_(-1)
+            blk.count.fill_(99)
+        (ace.verify_attestations if attest else ace.verify_batch)(ks, blocks)
+        torch.cuda.synchronize()
+        for k, (blk, (mask, count)) in enumerate(zip(blocks, want)):
+            m, c = blk.result()
+            assert c == count and np.array_equal(m, mask), k
+
+
+def test_graph_replays_of_changing_size(ace):
+    """One capture of the local form replayed for batches of a few and of many
+    wave tiles per workgroup, and for none."""
+    import torch
+    w, msg, off, tags, salt = sweep(300_000, 5_000, 1, 3)
+    d_msg = ace.to_device(msg)
+    ks = ace.midstate_keyset(ace.to_device(w.rev), salt, w.info)
+    g = ace.Graph(ks, 64, 1_200_000)
+    for cuts in ([0, 300_000], [0, 17, 17, 3_000, 200_001], [5, 6], [0, 0], list(range(0, 300_001, 5_000))):
+        print("graph blocks=%d" % (len(cuts) - 1), flush=True)
+        blocks = [ace.upload_block(None, off[a:b + 1], w.ids[a:b], tags[a:b], msg_dev=d_msg)
+                  for a, b in zip(cuts[:-1], cuts[1:])]
+        for blk in blocks:
+            blk.bitmask.fill_(-1)
+            blk.count.fill_(99)
+        for _ in range(2):
+            g.launch(blocks)
+        torch.cuda.synchronize()
+        for blk, a, b in zip(blocks, cuts[:-1], cuts[1:]):
+            m, c = blk.result()
+            mask, count = oracle.verify_batch(w.keys, msg, off[a:b + 1], w.ids[a:b], tags[a:b], 8)
+            assert c == count and np.array_equal(m, mask), (a, b)
+    g.close()

@@ -401,23 +401,25 @@ Fork *fork_ctx()
 constexpr uint64_t kCountWGs = 256;
 
 // Verify-kernel launches for the plan's key source, persistence and record form.
+// In-order launches: workgroups of one wave, spread over the CUs, of four where
+// they share a parameter set's preparation; `pairs`: of two waves per wave tile.
 template <bool PT, bool AT>
-void launch_ordered_t(unsigned g, unsigned threads, hipStream_t s, const Batch &bt, const KeySource &ks,
+void launch_ordered_t(bool pairs, unsigned g, hipStream_t s, const Batch &bt, const KeySource &ks,
                       const HkdfParams &hp, bool solo)
 {
-    hipLaunchKernelGGL((k_verify_ordered<PT, AT>), dim3(g), dim3(threads), 0, s, bt, ks, hp,
-                       (uint32_t)solo);
+    if (pairs) hipLaunchKernelGGL((k_verify_pair<PT, AT>), dim3(g), dim3(128), 0, s, bt, ks, hp, (uint32_t)solo);
+    else hipLaunchKernelGGL((k_verify_ordered<PT, AT>), dim3(g), dim3(PT ? kWG : 64), 0, s, bt, ks, hp);
 }
 
-void launch_ordered(bool attest, bool per_tx, unsigned g, unsigned threads, hipStream_t s, const Batch &bt,
+void launch_ordered(bool attest, bool per_tx, bool pairs, unsigned g, hipStream_t s, const Batch &bt,
                     const KeySource &ks, const HkdfParams &hp, bool solo)
 {
     if (attest) {
-        if (per_tx) launch_ordered_t<true, true>(g, threads, s, bt, ks, hp, solo);
-        else launch_ordered_t<false, true>(g, threads, s, bt, ks, hp, solo);
+        if (per_tx) launch_ordered_t<true, true>(pairs, g, s, bt, ks, hp, solo);
+        else launch_ordered_t<false, true>(pairs, g, s, bt, ks, hp, solo);
     } else {
-        if (per_tx) launch_ordered_t<true, false>(g, threads, s, bt, ks, hp, solo);
-        else launch_ordered_t<false, false>(g, threads, s, bt, ks, hp, solo);
+        if (per_tx) launch_ordered_t<true, false>(pairs, g, s, bt, ks, hp, solo);
+        else launch_ordered_t<false, false>(pairs, g, s, bt, ks, hp, solo);
     }
 }
 
@@ -518,7 +520,9 @@ int enqueue_stages(const Plan &p, const Batch &bt, const ace_keyset *keys, const
     // verify kernel waits for both.
     const bool per_tx = p.per_tx || (p.rev && form == kInOrder && !(p.flags & ACE_ORDERED));
     unsigned long long *const zero = graph || p.n_blocks > 1 ? nullptr : bt.one.count;  // else cleared already
-    const bool solo = zero && form == kInOrder && p.total_waves <= kWavesPerWG && p.total_tx;
+    // in order with two waves per wave tile while each wave has its SIMD to itself
+    const bool pairs = form == kInOrder && waves <= 2ull * cus;
+    const bool solo = zero && pairs && p.total_waves == 1;  // one workgroup stores the count itself
     bool cleared = !zero || solo;
     Fork *fk = nullptr;
     if (!p.rev) {
@@ -565,12 +569,12 @@ int enqueue_stages(const Plan &p, const Batch &bt, const ace_keyset *keys, const
     if (!binned) {
         prof_mark(prof, 2, s);
         if ((graph || p.total_tx) && form == kInOrder) {
-            // workgroups of one wave, spread over the CUs; of four where they
-            // share a parameter set's preparation or the whole call
-            const unsigned wpw = per_tx || solo ? kWavesPerWG : 1;
-            unsigned g = grid_for(waves, wpw, 0x7fffffffu);
-            if (graph) g = std::min<unsigned>(g, tn.verify_wgs_per_cu * cus * (kWavesPerWG / wpw));
-            launch_ordered(p.attest, per_tx, g, 64 * wpw, s, bt, ks, hp, solo);
+            unsigned g = (unsigned)waves;
+            if (!pairs) {
+                g = grid_for(waves, per_tx ? kWavesPerWG : 1, 0x7fffffffu);
+                if (graph) g = std::min<unsigned>(g, tn.verify_wgs_per_cu * cus * (per_tx ? 1 : kWavesPerWG));
+            }
+            launch_ordered(p.attest, per_tx, pairs, g, s, bt, ks, hp, solo);
             if ((rc = launch_status("k_verify_ordered launch"))) return rc;
         } else if (graph || p.total_tx) {
             const LocalShape sh = local_shape(waves, cus);
@@ -884,18 +888,16 @@ ACE_API int ace_merkle_roots(const ace_merkle_tree *trees, uint32_t n_trees, voi
 
     MerkleChunk chunk;
     memset(&chunk, 0, sizeof chunk);
-    uint64_t leaf0 = 0;
     for (uint32_t b = 0; b < n_trees; ++b) {
-        MerkleDesc &d = chunk.d[chunk.count++];
-        d.data = trees[b].d_data;
-        d.off = trees[b].d_off;
-        d.n = trees[b].n_leaves;
-        d.root = trees[b].d_root_out;
-        d.leaf0 = leaf0;
-        leaf0 += d.n;
+        const uint32_t at = chunk.count++;
+        chunk.data[at] = trees[b].d_data;
+        chunk.off[at] = trees[b].d_off;
+        chunk.root[at] = trees[b].d_root_out;
+        chunk.n[at] = (uint32_t)trees[b].n_leaves;  // at most ACE_MAX_TX
         if (chunk.count == kMerkleChunk || b + 1 == n_trees) {
-            hipLaunchKernelGGL(k_merkle_put, dim3(1), dim3(kMerkleChunk), 0, s, table, chunk);
+            hipLaunchKernelGGL(k_merkle_put, dim3(1), dim3(kPutThreads), 0, s, table, chunk);
             if ((rc = launch_status("k_merkle_put launch"))) return rc;
+            for (uint32_t i = 0; i < chunk.count; ++i) chunk.leaf0 += chunk.n[i];
             chunk.first = b + 1;
             chunk.count = 0;
         }
@@ -905,34 +907,54 @@ ACE_API int ace_merkle_roots(const ace_merkle_tree *trees, uint32_t n_trees, voi
                            table, n_trees, p.total, nodes);
         if ((rc = launch_status("k_merkle_leaves launch"))) return rc;
     }
-    // levels below k0 one launch each over all trees; from k0, where no tree
-    // has more than kTopNodes nodes, one launch for the rest
-    uint32_t k0 = 0;
-    for (uint32_t b = 0; b < n_trees; ++b)
-        while (((trees[b].n_leaves + (1ull << k0) - 1) >> k0) > kTopNodes) ++k0;
-    if (k0 > p.levels) k0 = p.levels;
-    if (k0) {
-        hipLaunchKernelGGL(k_merkle_plan, dim3(k0), dim3(kPlanThreads), 0, s, table, n_trees, P);
+    // Stages up to the one that finishes every tree in a workgroup of its own:
+    // a level over all trees per launch, or, once all trees together are no
+    // more than one chunk of kTopNodes per CU, ten levels of each chunk in LDS
+    // (one tree of 100,000 leaves 112 us, 126 with a launch per level).
+    auto nodes_at = [&](uint32_t level) {
+        uint64_t m = 0;
+        for (uint32_t b = 0; b < n_trees; ++b) m += (trees[b].n_leaves + (1ull << level) - 1) >> level;
+        return m;
+    };
+    struct Stage {
+        uint32_t k, log;  // level it starts from, levels it goes up
+        uint64_t groups;
+    };
+    Stage stage[kMaxStages];
+    MerkleShifts sh{};
+    uint32_t n_stages = 0, k = 0;
+    uint64_t widest = 0;
+    for (uint32_t b = 0; b < n_trees; ++b) widest = std::max<uint64_t>(widest, trees[b].n_leaves);
+    while (((widest + (1ull << k) - 1) >> k) > kTopNodes) {
+        Stage &g = stage[n_stages];
+        const uint64_t chunks = nodes_at(k + kTopLog);
+        g.k = k;
+        g.log = chunks <= (uint64_t)cu_count() ? kTopLog : 1;
+        g.groups = g.log == 1 ? nodes_at(k + 1) : chunks;
+        k += g.log;
+        sh.shift[n_stages++] = k;
+    }
+    const bool prefixes = n_stages && n_trees > 1;
+    if (prefixes) {
+        hipLaunchKernelGGL(k_merkle_plan, dim3(n_stages), dim3(kPlanThreads), 0, s, table, n_trees, sh, P);
         if ((rc = launch_status("k_merkle_plan launch"))) return rc;
     }
-    for (uint32_t k = 0; k < k0; ++k) {
-        // this level's pairs over all trees, as the plan kernel counts them
-        uint64_t pairs = 0;
-        for (uint32_t b = 0; b < n_trees; ++b) {
-            const uint64_t n = trees[b].n_leaves;
-            pairs += ((n + (1ull << k) - 1) >> k) >> 1;
+    for (uint32_t i = 0; i < n_stages; ++i) {
+        const Stage &g = stage[i];
+        const unsigned long long *row = prefixes ? P + (uint64_t)i * (n_trees + 1ull) : nullptr;
+        if (g.log == 1) {
+            hipLaunchKernelGGL(k_merkle_level, dim3((unsigned)((g.groups + kWG - 1) / kWG)), dim3(kWG), 0, s,
+                               table, n_trees, row, g.groups, g.k, nodes);
+            if ((rc = launch_status("k_merkle_level launch"))) return rc;
+        } else {
+            hipLaunchKernelGGL(k_merkle_chunk, dim3((unsigned)g.groups), dim3(kTopWG), 0, s, table, n_trees, row,
+                               g.k, 0u, nodes);
+            if ((rc = launch_status("k_merkle_chunk launch"))) return rc;
         }
-        if (!pairs) continue;
-        hipLaunchKernelGGL(k_merkle_level, dim3((unsigned)((pairs + kWG - 1) / kWG)), dim3(kWG), 0, s, table,
-                           n_trees, k, P + (uint64_t)k * (n_trees + 1ull), nodes);
-        if ((rc = launch_status("k_merkle_level launch"))) return rc;
     }
-    if (k0 < p.levels) {
-        hipLaunchKernelGGL(k_merkle_top, dim3(n_trees), dim3(kTopWG), 0, s, table, k0, nodes);
-        if ((rc = launch_status("k_merkle_top launch"))) return rc;
-    }
-    hipLaunchKernelGGL(k_merkle_out, dim3((n_trees + kWG - 1) / kWG), dim3(kWG), 0, s, table, n_trees, nodes);
-    return launch_status("k_merkle_out launch");
+    hipLaunchKernelGGL(k_merkle_chunk, dim3(n_trees), dim3(kTopWG), 0, s, table, n_trees,
+                       (const unsigned long long *)nullptr, k, 1u, nodes);
+    return launch_status("k_merkle_chunk launch");
 }
 
 ACE_API size_t ace_verify_workspace_size(const ace_keyset *keys, const ace_block *blocks,

@@ -91,8 +91,9 @@ __device__ __forceinline__ Totals totals(const Batch &bt)
 
 __device__ __forceinline__ DevBlock get_block(const Batch &bt, const Totals &T, uint32_t b)
 {
-    if (T.inline_one) return bt.one;
-    return bt.table[b];
+    DevBlock d = bt.one;  // scalar loads of the kernel arguments
+    if (!T.inline_one) d = bt.table[b];
+    return d;
 }
 
 // Last block whose prefix (selected by `field`) is <= x; empty blocks share
@@ -493,34 +494,32 @@ __device__ __forceinline__ bool verify_lane(bool live, const TxRef &t, const Hkd
 template <bool ATTEST>
 __device__ __forceinline__ bool load_tx(const DevBlock &d, uint64_t i, const KeySource &ks, TxRef &t)
 {
-    const uint64_t a = d.off[i], e = d.off[i + 1];
-    const uint32_t who = d.id[i];
+    const gptr64 off = (gptr64)d.off;
+    const uint64_t a = off[i], e = off[i + 1], area_end = off[d.n];
+    const uint32_t who = ((gptr)d.id)[i];
     const bool ok = who < ks.n_id && a <= e;
     t.msg = d.msg + a;
     t.L = ok ? e - a : 0;
     t.mid = ks.mid ? ks.mid + 16ull * (ok ? who : 0u) : nullptr;
     t.rev = ks.rev ? ks.rev + 32ull * (ok ? who : 0u) : nullptr;
     t.tag = d.tag + (uint64_t)check_stride<ATTEST>() * i;
-    t.overread_ok = ok && e + kOverread <= d.off[d.n];
+    t.overread_ok = ok && e + kOverread <= area_end;
     return ok;
 }
 
 // ------------------------------------------------------------------------------------------
 // k_verify, in-order form: wave tile w covers transactions 64w' .. 64w'+63 of
 // one block; the ballot is that block's two bitmask words, its population
-// count goes to the block's count (cleared before).  `solo`: the whole call is
-// one workgroup, which stores the count itself (nothing needs to clear it).
+// count goes to the block's count (cleared before).
 //
 // Bound by one wave's chain of compressions: it serves calls of at most one
 // wave per SIMD (and ACE_ORDERED), where a lone wave issues a VALU instruction
 // every 4.3 cycles, so whatever it waits for besides costs the call its time.
 // ------------------------------------------------------------------------------------------
 template <bool PER_TX_KEYS, bool ATTEST>
-__global__ void __launch_bounds__(kWG) ACE_WAVES(4) k_verify_ordered(Batch bt, KeySource ks, HkdfParams hp,
-                                                                     uint32_t solo)
+__global__ void __launch_bounds__(kWG) ACE_WAVES(4) k_verify_ordered(Batch bt, KeySource ks, HkdfParams hp)
 {
     __shared__ HkdfPrep prep;
-    __shared__ uint32_t part[kWavesPerWG];
     if constexpr (PER_TX_KEYS) {
         hkdf_prepare(hp, prep);
         __syncthreads();
@@ -529,7 +528,6 @@ __global__ void __launch_bounds__(kWG) ACE_WAVES(4) k_verify_ordered(Batch bt, K
     // grid-stride over wave tiles (wave-uniform loop bound)
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t wpw = blockDim.x >> 6;
-    uint32_t found = 0;  // solo: valid transactions of this wave
     for (uint64_t w = (uint64_t)blockIdx.x * wpw + wave; w < T.waves; w += (uint64_t)gridDim.x * wpw) {
         const uint32_t b = find_block<1>(bt, T, w);
         const DevBlock d = get_block(bt, T, b);
@@ -544,18 +542,289 @@ __global__ void __launch_bounds__(kWG) ACE_WAVES(4) k_verify_ordered(Batch bt, K
         if (lane_id() == 0) {
             d.bitmask[i0 >> 5] = (uint32_t)m;
             if (i0 + 32 < d.n) d.bitmask[(i0 >> 5) + 1] = (uint32_t)(m >> 32);
-            if (!solo && m) atomicAdd(d.count, (unsigned long long)__popcll(m));
+            if (m) atomicAdd(d.count, (unsigned long long)__popcll(m));
         }
-        found = (uint32_t)__popcll(m);
     }
-    if (solo) {
-        if (lane_id() == 0) part[wave] = found;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            uint32_t s = 0;
-            for (uint32_t k = 0; k < wpw; ++k) s += part[k];
-            *bt.one.count = s;
+}
+
+// ------------------------------------------------------------------------------------------
+// k_verify, pair form, for the smallest calls: two waves share the work of one
+// wave tile.  A lane's chain of compressions is serial, but only the rounds of
+// a block depend on the chain: the second wave loads and pads message block
+// b + 1 and expands its schedule (about 750 instructions) while the first runs
+// the 64 rounds of block b (about 900) on K[t] + W[t] read from LDS.  Where a
+// block's words are the chain itself (HMAC's outer block, HKDF), the first wave
+// starts its rounds 0..15 at once and the second expands the words of rounds
+// 16..63 sixteen at a time ahead of it; the two midstates of a key go one to
+// each wave.
+//
+// Bound by that chain: a lone wave takes 2.5 us for a whole compression and
+// about 1.7 for the rounds alone.  It needs two waves' SIMDs per tile, so it
+// serves calls of up to half as many tiles as there are SIMDs.
+// ------------------------------------------------------------------------------------------
+struct PairLds {
+    U4 kw[2][16][64];  // K[t] + W[t] of two message blocks: [t / 4][lane]
+    U4 tail[12][64];   // the same of rounds 16..63 of a block made from the chain
+    U4 down[2][64];    // eight words per lane from the first wave to the second
+    U4 up[2][64];      // and back
+    uint32_t blocks;   // message blocks of the tile's longest message
+};
+
+__device__ __forceinline__ void put8(U4 (&x)[2][64], const State &s)
+{
+    const uint32_t l = lane_id();
+    x[0][l] = U4{s.h[0], s.h[1], s.h[2], s.h[3]};
+    x[1][l] = U4{s.h[4], s.h[5], s.h[6], s.h[7]};
+}
+__device__ __forceinline__ State get8(const U4 (&x)[2][64])
+{
+    const uint32_t l = lane_id();
+    const U4 a = x[0][l], b = x[1][l];
+    return State{{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w}};
+}
+
+// Rounds 16 q .. 16 q + 15 from K[t] + W[t] in LDS.
+__device__ __forceinline__ void rounds16(uint32_t (&v)[8], const U4 (*kw)[64])
+{
+    const uint32_t l = lane_id();
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const U4 k = kw[c][l];
+        const uint32_t w[4] = {k.x, k.y, k.z, k.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            round_step(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], w[j], 0u);
+    }
+}
+__device__ __forceinline__ void add_state(State &s, const uint32_t (&v)[8])
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s.h[i] += v[i];
+}
+
+// Sixteen schedule words W[16 q ..] (q > 0: from the sixteen before) to LDS
+// with their round constants added.
+template <int Q>
+__device__ __forceinline__ void expand16(uint32_t (&W)[16], U4 (*kw)[64])
+{
+    const uint32_t l = lane_id();
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        uint32_t o[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int j = 4 * c + i;
+            if (Q > 0)
+                W[j] = small_sigma1(W[(j - 2) & 15]) + W[(j - 7) & 15] + small_sigma0(W[(j - 15) & 15]) + W[j];
+            o[i] = W[j] + kRound[16 * Q + j];
         }
+        kw[c][l] = U4{o[0], o[1], o[2], o[3]};
+    }
+}
+
+// s <- F(s, m || 0x80 || 0 || 768) for a 32-byte message m after a 64-byte key
+// block: the first wave's part, and the second's (four barriers each).
+__device__ __forceinline__ void pair_tail_rounds(PairLds &L, State &s, const State &m)
+{
+    put8(L.down, m);
+    __syncthreads();
+    uint32_t v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = s.h[i];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+        const uint32_t w = t < 8 ? m.h[t & 7] : (t == 8 ? 0x80000000u : (t == 15 ? 768u : 0u));
+        round_step(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], w, kRound[t]);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        __syncthreads();
+        rounds16(v, &L.tail[4 * q]);
+    }
+    add_state(s, v);
+}
+__device__ __forceinline__ void pair_tail_schedule(PairLds &L)
+{
+    __syncthreads();
+    const State m = get8(L.down);
+    uint32_t W[16];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) W[i] = m.h[i];
+    W[8] = 0x80000000u;
+#pragma unroll
+    for (int i = 9; i < 15; ++i) W[i] = 0u;
+    W[15] = 768u;
+    expand16<1>(W, &L.tail[0]);
+    __syncthreads();
+    expand16<2>(W, &L.tail[4]);
+    __syncthreads();
+    expand16<3>(W, &L.tail[8]);
+    __syncthreads();
+}
+
+// A block's whole schedule.
+__device__ __forceinline__ void pair_schedule(uint32_t (&W)[16], U4 (*kw)[64])
+{
+    expand16<0>(W, kw);
+    expand16<1>(W, kw + 4);
+    expand16<2>(W, kw + 8);
+    expand16<3>(W, kw + 12);
+}
+__device__ __forceinline__ void pair_rounds(State &s, const U4 (*kw)[64])
+{
+    uint32_t v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = s.h[i];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) rounds16(v, kw + 4 * q);
+    add_state(s, v);
+}
+
+template <bool PER_TX_KEYS, bool ATTEST>
+__global__ void __launch_bounds__(128) k_verify_pair(Batch bt, KeySource ks, HkdfParams hp, uint32_t solo)
+{
+    __shared__ PairLds L;
+    __shared__ HkdfPrep prep;
+    const Totals T = totals(bt);
+    const uint32_t w = blockIdx.x;
+    if (w >= T.waves) return;  // the whole workgroup (a replay smaller than its capture)
+    const bool first = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0;
+    const DevBlock d = get_block(bt, T, find_block<1>(bt, T, w));
+    const uint64_t i0 = 64ull * (w - d.wave0);
+    const uint64_t i = i0 + lane_id();
+    TxRef t{};
+    bool live = false;
+    if (i < d.n) live = load_tx<ATTEST>(d, i, ks, t);
+    const LaneGeom g = lane_geom<ATTEST>(live, t);
+
+    // the second wave's message side: block b's window in D, loaded a block ahead
+    uint32_t D[17];
+    auto load = [&](uint32_t b) {
+        if (b < g.nb) load_window(D, g.A0 + 16ull * b, (int64_t)t.L - 64ll * b, t.overread_ok, g.A0, g.last, b);
+    };
+    auto produce = [&](uint32_t b) {
+        if (b < g.nb) {
+            uint32_t W[16];
+            window_words<0, 1>(W, D, g.sel);
+            load(b + 1);
+            const int64_t rb = (int64_t)t.L - 64ll * b;
+            if (rb < 64) pad_block(W, g, rb, b);
+            pair_schedule(W, L.kw[b & 1]);
+        }
+    };
+    uint32_t C[check_words<ATTEST>()];
+#pragma unroll
+    for (int k = 0; k < check_words<ATTEST>(); ++k) C[k] = 0;
+    if (live) load_check<ATTEST>(t.tag, C);
+    State ipad = initial_state(), opad = ipad;
+    uint32_t rv[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) rv[k] = 0;
+    if (first) {
+        if (live) {
+            if constexpr (PER_TX_KEYS) {
+                const uint32_t *p = reinterpret_cast<const uint32_t *>(t.rev);
+                const U4 a = load16(p), b = load16(p + 4);
+                rv[0] = a.x; rv[1] = a.y; rv[2] = a.z; rv[3] = a.w;
+                rv[4] = b.x; rv[5] = b.y; rv[6] = b.z; rv[7] = b.w;
+            } else {
+                uint32_t M[16];
+                load_midstates(t.mid, M);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) { ipad.h[k] = M[k]; opad.h[k] = M[8 + k]; }
+            }
+        }
+        // one wave's count of blocks for both (the barriers below follow it)
+        uint32_t m = 0;
+        for (unsigned long long more; (more = __ballot(g.nb > m)) != 0;)
+            m = __builtin_amdgcn_readlane(g.nb, __builtin_ctzll(more));
+        if (lane_id() == 0) L.blocks = m;
+    } else {
+        load(0);
+    }
+    if constexpr (PER_TX_KEYS) hkdf_prepare(hp, prep);
+    __syncthreads();
+    const uint32_t blocks = uniform32(L.blocks);
+    if constexpr (PER_TX_KEYS) {
+        // as derive_lane, the steps shared out
+        if (first) {
+            State m, x, prk;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                m.h[k] = bswap32(rv[k]);
+                x.h[k] = prep.salt_ipad[k];
+                prk.h[k] = prep.salt_opad[k];
+            }
+            pair_tail_rounds(L, x, m);
+            pair_tail_rounds(L, prk, x);
+            put8(L.down, prk);
+            __syncthreads();
+            State pi = hmac_midstate<0x36363636u>(prk);
+            const uint32_t nq = prep.info_blocks;
+            for (uint32_t q = 0; q < nq; ++q) compress_kw(pi, prep.info_kw[q]);
+            __syncthreads();
+            State key = get8(L.up);
+            pair_tail_rounds(L, key, pi);
+            put8(L.down, key);
+            __syncthreads();
+            ipad = hmac_midstate<0x36363636u>(key);
+        } else {
+            pair_tail_schedule(L);
+            pair_tail_schedule(L);
+            __syncthreads();
+            put8(L.up, hmac_midstate<0x5c5c5c5cu>(get8(L.down)));
+            produce(0);
+            __syncthreads();
+            pair_tail_schedule(L);
+            __syncthreads();
+            put8(L.up, hmac_midstate<0x5c5c5c5cu>(get8(L.down)));
+        }
+    } else if (!first) {
+        produce(0);
+    }
+    State S = ATTEST ? initial_state() : ipad;
+    for (uint32_t b = 0; b < blocks; ++b) {
+        __syncthreads();
+        if (first) {
+            if (b < g.nb) pair_rounds(S, L.kw[b & 1]);
+        } else if (b + 1 < blocks) {
+            produce(b + 1);
+        } else if constexpr (ATTEST) {
+            // the HMAC's block over obj_hash || domain (see lane_result)
+            uint32_t W[16];
+#pragma unroll
+            for (int k = 0; k < 10; ++k) W[k] = bswap32(C[k]);
+            W[10] = 0x80000000u;
+#pragma unroll
+            for (int k = 11; k < 15; ++k) W[k] = 0u;
+            W[15] = (64u + 40u) * 8u;
+            pair_schedule(W, L.kw[(b + 1) & 1]);
+        }
+    }
+    __syncthreads();
+    if (!first) {
+        pair_tail_schedule(L);
+        return;  // no barrier follows
+    }
+    if constexpr (PER_TX_KEYS) opad = get8(L.up);
+    uint32_t diff = 0;
+    if constexpr (ATTEST) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) diff = or_xor(diff, S.h[k], bswap32(C[k]));
+        S = ipad;
+        pair_rounds(S, L.kw[blocks & 1]);
+    }
+    pair_tail_rounds(L, opad, S);
+    constexpr int c0 = ATTEST ? 10 : 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) diff = or_xor(diff, opad.h[k], bswap32(C[c0 + k]));
+    const unsigned long long m = __ballot(live && diff == 0);
+    if (lane_id() == 0) {
+        d.bitmask[i0 >> 5] = (uint32_t)m;
+        if (i0 + 32 < d.n) d.bitmask[(i0 >> 5) + 1] = (uint32_t)(m >> 32);
+        const unsigned long long c = __popcll(m);
+        if (solo) *d.count = c;
+        else if (c) atomicAdd(d.count, c);
     }
 }
 
@@ -1253,10 +1522,14 @@ __global__ void k_put_descs(DevBlock *table, DescChunk c)
 }
 
 // Explicit instantiations used by the host entry points.
-template __global__ void k_verify_ordered<false, false>(Batch, KeySource, HkdfParams, uint32_t);
-template __global__ void k_verify_ordered<true, false>(Batch, KeySource, HkdfParams, uint32_t);
-template __global__ void k_verify_ordered<false, true>(Batch, KeySource, HkdfParams, uint32_t);
-template __global__ void k_verify_ordered<true, true>(Batch, KeySource, HkdfParams, uint32_t);
+template __global__ void k_verify_ordered<false, false>(Batch, KeySource, HkdfParams);
+template __global__ void k_verify_pair<false, false>(Batch, KeySource, HkdfParams, uint32_t);
+template __global__ void k_verify_ordered<true, false>(Batch, KeySource, HkdfParams);
+template __global__ void k_verify_pair<true, false>(Batch, KeySource, HkdfParams, uint32_t);
+template __global__ void k_verify_ordered<false, true>(Batch, KeySource, HkdfParams);
+template __global__ void k_verify_pair<false, true>(Batch, KeySource, HkdfParams, uint32_t);
+template __global__ void k_verify_ordered<true, true>(Batch, KeySource, HkdfParams);
+template __global__ void k_verify_pair<true, true>(Batch, KeySource, HkdfParams, uint32_t);
 #define ACE_LOCAL(R, N) template __global__ void k_verify_local<R, N>(Batch, KeySource);
 ACE_LOCAL(false, 8)
 ACE_LOCAL(true, 8)

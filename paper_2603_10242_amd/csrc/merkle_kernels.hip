@@ -13,13 +13,18 @@
 // level expects it.
 //
 //   k_merkle_leaves  one leaf per lane: SHA-256 of its bytes into its slot.
-//   k_merkle_plan    per level (one workgroup each), exclusive prefix of each
-//                    tree's pair count.
+//   k_merkle_plan    per reducing stage (one workgroup each), exclusive prefix
+//                    of each tree's groups.
 //   k_merkle_level   one parent per lane at level k -> k + 1 (two blocks:
 //                    the 64 child bytes, then the constant padding block).
-//   k_merkle_top     the levels from k0 up, where every tree has at most
-//                    kTopNodes nodes: one workgroup per tree, in LDS.
-//   k_merkle_out     roots to the callers' 32-byte outputs.
+//   k_merkle_chunk   the narrow levels: a workgroup reduces up to kTopNodes
+//                    nodes of a tree in LDS; the last such stage writes the roots.
+//
+// Bound by VALU issue where a level fills the chip and by one wave's chain of
+// two compressions per level where it does not.  (Groups of eight leaves or
+// nodes reduced in a lane's registers, three levels per launch, measured slower:
+// 7.66M leaves of 256 trees 1,183 us against 1,163 with a launch per level, since
+// the wide levels run at 95% of the issue rate as they are.)
 
 namespace ace {
 
@@ -31,11 +36,17 @@ struct MerkleDesc {
     uint64_t leaf0;  // global index of the first leaf
 };
 
-constexpr uint32_t kMerkleChunk = 64;
+// Trees passed by value to the kernel that writes the table (3,944 bytes of
+// kernel arguments): two launches for 256 trees.
+constexpr uint32_t kMerkleChunk = 140;
 struct MerkleChunk {
-    MerkleDesc d[kMerkleChunk];
+    const uint8_t *data[kMerkleChunk];
+    const uint64_t *off[kMerkleChunk];
+    uint8_t *root[kMerkleChunk];
+    uint32_t n[kMerkleChunk];
     uint32_t first;
     uint32_t count;
+    uint64_t leaf0;  // global index of the chunk's first leaf
 };
 
 // The second block of every parent is the padding of a 64-byte message
@@ -76,10 +87,21 @@ __device__ __forceinline__ void compress_pad64(State &s)
     s.h[4] += e; s.h[5] += f; s.h[6] += g; s.h[7] += h;
 }
 
-__global__ void k_merkle_put(MerkleDesc *table, MerkleChunk c)
+constexpr uint32_t kPutThreads = 256;
+__global__ void __launch_bounds__(kPutThreads) k_merkle_put(MerkleDesc *table, MerkleChunk c)
 {
+    __shared__ uint64_t part[kPutThreads];
     const uint32_t t = threadIdx.x;
-    if (t < c.count) table[c.first + t] = c.d[t];
+    const uint64_t n = t < c.count ? c.n[t] : 0;
+    part[t] = n;
+    __syncthreads();
+    for (uint32_t s = 1; s < kPutThreads; s <<= 1) {  // inclusive scan (Hillis-Steele)
+        const uint64_t add = t >= s ? part[t - s] : 0;
+        __syncthreads();
+        part[t] += add;
+        __syncthreads();
+    }
+    if (t < c.count) table[c.first + t] = MerkleDesc{c.data[t], c.off[t], n, c.root[t], c.leaf0 + part[t] - n};
 }
 
 // Last i < n with key(i) <= x, for keys that do not decrease (equal keys:
@@ -248,26 +270,59 @@ __global__ void __launch_bounds__(kWG) k_merkle_leaves(const MerkleDesc *__restr
     }
 }
 
-// P[k * (n_trees + 1) + b] = pairs at level k of trees before b; the last
-// entry of each row is the level's total.  Workgroup k scans level k.
+// Parent of two nodes: SHA-256 of their 64 bytes, the second block of which is
+// constant.
+__device__ __forceinline__ State merkle_parent(const State &l, const State &r)
+{
+    uint32_t W[16];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) { W[j] = l.h[j]; W[8 + j] = r.h[j]; }
+    State S = initial_state();
+    compress_block(S, W);
+    compress_pad64(S);
+    return S;
+}
+
+__device__ __forceinline__ State load_node(const uint32_t *q)
+{
+    const U4 a = load16(q), b = load16(q + 4);
+    State S;
+    S.h[0] = a.x; S.h[1] = a.y; S.h[2] = a.z; S.h[3] = a.w;
+    S.h[4] = b.x; S.h[5] = b.y; S.h[6] = b.z; S.h[7] = b.w;
+    return S;
+}
+
+__device__ __forceinline__ void store_node(uint32_t *q, const State &S)
+{
+#pragma unroll
+    for (int j = 0; j < 8; ++j) q[j] = S.h[j];
+}
+
+// Row r of P: exclusive prefix over the trees of ceil(n / 2^shift[r]), the
+// groups of the stage that reduces 2^shift[r] leaves to a node.  Workgroup r
+// scans row r.
 constexpr uint32_t kPlanThreads = 1024;
+constexpr uint32_t kMaxStages = 32;  // levels of the largest tree
+struct MerkleShifts {
+    uint32_t shift[kMaxStages];
+};
+__device__ __forceinline__ uint64_t merkle_nodes(uint64_t n, uint32_t level)
+{
+    return (n + (1ull << level) - 1) >> level;
+}
+
 __global__ void __launch_bounds__(kPlanThreads) k_merkle_plan(const MerkleDesc *__restrict__ table,
-                                                              uint32_t n_trees,
+                                                              uint32_t n_trees, MerkleShifts sh,
                                                               unsigned long long *__restrict__ P)
 {
     __shared__ unsigned long long part[kPlanThreads];
     const uint32_t t = threadIdx.x;
-    const uint32_t k = blockIdx.x;
-    unsigned long long *row = P + (uint64_t)k * (n_trees + 1);
+    const uint32_t shift = sh.shift[blockIdx.x];
+    unsigned long long *row = P + (uint64_t)blockIdx.x * (n_trees + 1);
     unsigned long long running = 0;
     for (uint32_t c = 0; c < n_trees; c += kPlanThreads) {
         const uint32_t b = c + t;
-        unsigned long long v = 0;
-        if (b < n_trees) {
-            const uint64_t n = table[b].n;
-            const uint64_t m = k >= 63 ? (n ? 1 : 0) : (n + (1ull << k) - 1) >> k;
-            v = m >> 1;
-        }
+        const unsigned long long v = b < n_trees ? merkle_nodes(table[b].n, shift) : 0;
         part[t] = v;
         __syncthreads();
         // Hillis-Steele inclusive scan
@@ -284,88 +339,85 @@ __global__ void __launch_bounds__(kPlanThreads) k_merkle_plan(const MerkleDesc *
     if (t == 0) row[n_trees] = running;
 }
 
+// Group q of a stage: its tree, and its index among the tree's groups.
+__device__ __forceinline__ uint32_t merkle_group(const unsigned long long *__restrict__ row,
+                                                 uint32_t n_trees, uint64_t q, uint64_t &j)
+{
+    j = q;
+    if (n_trees == 1) return 0;
+    const uint32_t b = last_at_or_below(n_trees, q, [&](uint32_t i) { return row[i]; });
+    j = q - row[b];
+    return b;
+}
+
 __global__ void __launch_bounds__(kWG) k_merkle_level(const MerkleDesc *__restrict__ table,
-                                                      uint32_t n_trees, uint32_t k,
-                                                      const unsigned long long *__restrict__ Pk,
+                                                      uint32_t n_trees,
+                                                      const unsigned long long *__restrict__ row,
+                                                      uint64_t n_groups, uint32_t k,
                                                       uint32_t *__restrict__ nodes)
 {
     const uint64_t q = (uint64_t)blockIdx.x * kWG + threadIdx.x;
-    const bool live = q < Pk[n_trees];
-    uint32_t W[16];
-    uint64_t left = 0;
+    bool live = q < n_groups;
+    State l = initial_state(), r = l;
+    uint32_t *o = nodes;
     if (live) {
-        // last tree whose prefix is <= q
-        const uint32_t lo = last_at_or_below(n_trees, q, [&](uint32_t i) { return Pk[i]; });
-        const uint64_t p = q - Pk[lo];
-        left = table[lo].leaf0 + ((2 * p) << k);
-        const uint64_t right = left + (1ull << k);
-        const uint32_t *a = nodes + 8ull * left;
-        const uint32_t *b = nodes + 8ull * right;
-        const U4 a0 = load16(a), a1 = load16(a + 4), b0 = load16(b), b1 = load16(b + 4);
-        W[0] = a0.x; W[1] = a0.y; W[2] = a0.z; W[3] = a0.w;
-        W[4] = a1.x; W[5] = a1.y; W[6] = a1.z; W[7] = a1.w;
-        W[8] = b0.x; W[9] = b0.y; W[10] = b0.z; W[11] = b0.w;
-        W[12] = b1.x; W[13] = b1.y; W[14] = b1.z; W[15] = b1.w;
-    } else {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) W[j] = 0;
+        uint64_t j;
+        const MerkleDesc &d = table[merkle_group(row, n_trees, q, j)];
+        live = 2 * j + 1 < merkle_nodes(d.n, k);  // an unpaired last node stays where it is
+        o = nodes + 8ull * (d.leaf0 + ((2 * j) << k));
+        if (live) {
+            l = load_node(o);
+            r = load_node(o + (8ull << k));
+        }
     }
     if (__ballot(live) == 0) return;
-    State S = initial_state();
-    compress_block(S, W);
-    compress_pad64(S);  // the 64-byte message's padding block
-    if (live) {
-        uint32_t *o = nodes + 8ull * left;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) o[j] = S.h[j];
-    }
+    const State S = merkle_parent(l, r);
+    if (live) store_node(o, S);
 }
 
-// The narrow top of every tree in one launch: workgroup b takes tree b from
-// level k0 (at most kTopNodes nodes there) to its root in LDS, one parent per
-// lane and level, and writes the root to the tree's first slot.  One launch
-// per level up there cost more in launches than in hashing.
+// The narrow levels: a workgroup takes a chunk of kTopNodes nodes of level k of
+// a tree (row: prefix of the trees' chunks) and reduces it in LDS, one parent per
+// lane and level, to the node of level k + kTopLog that it is.  `last`: every
+// tree is one chunk, whose node is the root and goes to the caller.
 constexpr uint32_t kTopWG = 512;
 constexpr uint32_t kTopNodes = 2 * kTopWG;
-__global__ void __launch_bounds__(kTopWG) k_merkle_top(const MerkleDesc *__restrict__ table, uint32_t k0,
-                                                       uint32_t *__restrict__ nodes)
+constexpr uint32_t kTopLog = 10;
+static_assert(kTopNodes == 1u << kTopLog, "a chunk is a full subtree");
+__global__ void __launch_bounds__(kTopWG) k_merkle_chunk(const MerkleDesc *__restrict__ table,
+                                                         uint32_t n_trees,
+                                                         const unsigned long long *__restrict__ row,
+                                                         uint32_t k, uint32_t last,
+                                                         uint32_t *__restrict__ nodes)
 {
     __shared__ uint32_t node[kTopNodes][8];
-    const MerkleDesc d = table[blockIdx.x];
+    uint64_t c = 0;
+    const MerkleDesc d = table[last ? blockIdx.x : merkle_group(row, n_trees, blockIdx.x, c)];
     const uint32_t t = threadIdx.x;
-    // nodes of the tree at level k0 (the host picks k0 so that m <= kTopNodes)
-    uint32_t m = d.n ? (uint32_t)((d.n + (1ull << k0) - 1) >> k0) : 0u;
-    if (m <= 1) return;  // the whole workgroup: the root is already in place
+    const uint64_t left = merkle_nodes(d.n, k) - (c << kTopLog);
+    uint32_t m = left < kTopNodes ? (uint32_t)left : kTopNodes;
+    if (m <= 1 && !last) return;  // the whole workgroup: the node is already in place
+    uint32_t *const base = nodes + 8ull * (d.leaf0 + (c << (kTopLog + k)));
     for (uint32_t j = t; j < m; j += kTopWG) {
-        const uint32_t *q = nodes + 8ull * (d.leaf0 + ((uint64_t)j << k0));
-        const U4 a = load16(q), b = load16(q + 4);
-        node[j][0] = a.x; node[j][1] = a.y; node[j][2] = a.z; node[j][3] = a.w;
-        node[j][4] = b.x; node[j][5] = b.y; node[j][6] = b.z; node[j][7] = b.w;
+        const State S = load_node(base + (8ull * j << k));
+        store_node(node[j], S);
     }
     __syncthreads();
     while (m > 1) {  // uniform
         const uint32_t pairs = m >> 1;
         const bool act = t < pairs;
-        State S = initial_state();
+        State S;
         if (act) {
-            uint32_t W[16];
+            State l, r;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                W[j] = node[2 * t][j];
-                W[8 + j] = node[2 * t + 1][j];
-            }
-            compress_block(S, W);
-            compress_pad64(S);  // the 64-byte message's padding block
+            for (int j = 0; j < 8; ++j) { l.h[j] = node[2 * t][j]; r.h[j] = node[2 * t + 1][j]; }
+            S = merkle_parent(l, r);
         }
         // an unpaired last node moves up unchanged, to index `pairs`
         uint32_t carry[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) carry[j] = node[m - 1][j];
         __syncthreads();
-        if (act) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) node[t][j] = S.h[j];
-        }
+        if (act) store_node(node[t], S);
         if ((m & 1) && t == 0) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) node[pairs][j] = carry[j];
@@ -373,29 +425,22 @@ __global__ void __launch_bounds__(kTopWG) k_merkle_top(const MerkleDesc *__restr
         __syncthreads();
         m = pairs + (m & 1);
     }
-    if (t < 8) nodes[8ull * d.leaf0 + t] = node[0][t];
-}
-
-__global__ void __launch_bounds__(kWG) k_merkle_out(const MerkleDesc *__restrict__ table,
-                                                    uint32_t n_trees,
-                                                    const uint32_t *__restrict__ nodes)
-{
-    const uint32_t b = blockIdx.x * kWG + threadIdx.x;
-    const bool live = b < n_trees;
-    MerkleDesc d{};
-    if (live) d = table[b];
-    // SHA-256 of the empty string for a tree without leaves
-    State S;
-    sha256_bytes(live && d.n == 0, nullptr, 0, S);
-    if (!live) return;
-    if (d.n) {
-        const uint32_t *q = nodes + 8ull * d.leaf0;
+    if (last) {
+        if (t >= 64) return;
+        State S = initial_state();
+        if (d.n == 0) {
+            sha256_bytes(true, nullptr, 0, S);  // no leaves: SHA-256 of the empty string
+        } else {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) S.h[j] = q[j];
+            for (int j = 0; j < 8; ++j) S.h[j] = node[0][j];
+        }
+        uint32_t *o = reinterpret_cast<uint32_t *>(d.root);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (t == 0) o[j] = bswap32(S.h[j]);
+    } else if (t < 8) {
+        base[t] = node[0][t];
     }
-    uint32_t *o = reinterpret_cast<uint32_t *>(d.root);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) o[j] = bswap32(S.h[j]);
 }
 
 }  // namespace ace

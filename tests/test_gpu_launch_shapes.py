@@ -115,3 +115,26 @@ def test_graph_replays_of_changing_size(ace):
             mask, count = oracle.verify_batch(w.keys, msg, off[a:b + 1], w.ids[a:b], tags[a:b], 8)
             assert c == count and np.array_equal(m, mask), (a, b)
     g.close()
+
+
+@pytest.mark.parametrize("sizes", [[100_003], [7_000] * 36 + [0, 1], [3] * 139 + [1024], [5] * 140 + [1025],
+                                   [2] * 281, [262_145, 1, 2_000]])
+def test_merkle_stages(ace, sizes):
+    """Trees reduced by levels, by chunks of 1,024 nodes and by both, and tables
+    of one, two and three launches."""
+    import torch
+    r = np.random.default_rng(len(sizes) + sizes[0])
+    n = sum(sizes)
+    off = np.zeros(n + 1, np.uint64)
+    np.cumsum(r.choice([72, 72, 72, 0, 40, 130], n), out=off[1:])
+    data = r.integers(0, 256, int(off[-1]) + 1, dtype=np.uint8)
+    print("merkle stages %s" % sizes[:3], flush=True)
+    d_data = ace.to_device(data)
+    roots = torch.zeros((len(sizes), 32), dtype=torch.uint8, device="cuda")
+    trees, at = [], 0
+    for k, s in enumerate(sizes):
+        trees.append((d_data, ace.to_device(off[at:at + s + 1]), s, roots[k]))
+        at += s
+    ace.merkle_roots(trees)
+    torch.cuda.synchronize()
+    assert np.array_equal(roots.cpu().numpy(), oracle.merkle_roots(data, off, sizes))

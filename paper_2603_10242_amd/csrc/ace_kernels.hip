@@ -562,35 +562,43 @@ __global__ void __launch_bounds__(kWG) ACE_WAVES(4) k_verify_ordered(Batch bt, K
 // about 1.7 for the rounds alone.  It needs two waves' SIMDs per tile, so it
 // serves calls of up to half as many tiles as there are SIMDs.
 // ------------------------------------------------------------------------------------------
+struct alignas(16) Q4 {  // one 16-byte LDS access
+    uint32_t x, y, z, w;
+};
 struct PairLds {
-    U4 kw[2][16][64];  // K[t] + W[t] of two message blocks: [t / 4][lane]
-    U4 tail[12][64];   // the same of rounds 16..63 of a block made from the chain
-    U4 down[2][64];    // eight words per lane from the first wave to the second
-    U4 up[2][64];      // and back
+    Q4 kw[2][16][64];  // K[t] + W[t] of two message blocks: [t / 4][lane]
+    Q4 tail[12][64];   // the same of rounds 16..63 of a block made from the chain
+    Q4 down[2][64];    // eight words per lane from the first wave to the second
+    Q4 up[2][64];      // and back
     uint32_t blocks;   // message blocks of the tile's longest message
 };
 
-__device__ __forceinline__ void put8(U4 (&x)[2][64], const State &s)
+__device__ __forceinline__ void put8(Q4 (&x)[2][64], const State &s)
 {
     const uint32_t l = lane_id();
-    x[0][l] = U4{s.h[0], s.h[1], s.h[2], s.h[3]};
-    x[1][l] = U4{s.h[4], s.h[5], s.h[6], s.h[7]};
+    x[0][l] = Q4{s.h[0], s.h[1], s.h[2], s.h[3]};
+    x[1][l] = Q4{s.h[4], s.h[5], s.h[6], s.h[7]};
 }
-__device__ __forceinline__ State get8(const U4 (&x)[2][64])
+__device__ __forceinline__ State get8(const Q4 (&x)[2][64])
 {
     const uint32_t l = lane_id();
-    const U4 a = x[0][l], b = x[1][l];
+    const Q4 a = x[0][l], b = x[1][l];
     return State{{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w}};
 }
 
-// Rounds 16 q .. 16 q + 15 from K[t] + W[t] in LDS.
-__device__ __forceinline__ void rounds16(uint32_t (&v)[8], const U4 (*kw)[64])
+// 16 N rounds from K[t] + W[t] in LDS.  All the words are read first (the
+// compiler, left to itself, reads them just before their rounds and waits).
+template <int N>
+__device__ __forceinline__ void rounds16(uint32_t (&v)[8], const Q4 (*kw)[64])
 {
     const uint32_t l = lane_id();
+    Q4 k[4 * N];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const U4 k = kw[c][l];
-        const uint32_t w[4] = {k.x, k.y, k.z, k.w};
+    for (int c = 0; c < 4 * N; ++c) k[c] = kw[c][l];
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int c = 0; c < 4 * N; ++c) {
+        const uint32_t w[4] = {k[c].x, k[c].y, k[c].z, k[c].w};
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             round_step(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], w[j], 0u);
@@ -605,7 +613,7 @@ __device__ __forceinline__ void add_state(State &s, const uint32_t (&v)[8])
 // Sixteen schedule words W[16 q ..] (q > 0: from the sixteen before) to LDS
 // with their round constants added.
 template <int Q>
-__device__ __forceinline__ void expand16(uint32_t (&W)[16], U4 (*kw)[64])
+__device__ __forceinline__ void expand16(uint32_t (&W)[16], Q4 (*kw)[64])
 {
     const uint32_t l = lane_id();
 #pragma unroll
@@ -618,7 +626,7 @@ __device__ __forceinline__ void expand16(uint32_t (&W)[16], U4 (*kw)[64])
                 W[j] = small_sigma1(W[(j - 2) & 15]) + W[(j - 7) & 15] + small_sigma0(W[(j - 15) & 15]) + W[j];
             o[i] = W[j] + kRound[16 * Q + j];
         }
-        kw[c][l] = U4{o[0], o[1], o[2], o[3]};
+        kw[c][l] = Q4{o[0], o[1], o[2], o[3]};
     }
 }
 
@@ -639,7 +647,7 @@ __device__ __forceinline__ void pair_tail_rounds(PairLds &L, State &s, const Sta
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
         __syncthreads();
-        rounds16(v, &L.tail[4 * q]);
+        rounds16<1>(v, &L.tail[4 * q]);
     }
     add_state(s, v);
 }
@@ -663,20 +671,19 @@ __device__ __forceinline__ void pair_tail_schedule(PairLds &L)
 }
 
 // A block's whole schedule.
-__device__ __forceinline__ void pair_schedule(uint32_t (&W)[16], U4 (*kw)[64])
+__device__ __forceinline__ void pair_schedule(uint32_t (&W)[16], Q4 (*kw)[64])
 {
     expand16<0>(W, kw);
     expand16<1>(W, kw + 4);
     expand16<2>(W, kw + 8);
     expand16<3>(W, kw + 12);
 }
-__device__ __forceinline__ void pair_rounds(State &s, const U4 (*kw)[64])
+__device__ __forceinline__ void pair_rounds(State &s, const Q4 (*kw)[64])
 {
     uint32_t v[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = s.h[i];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) rounds16(v, kw + 4 * q);
+    rounds16<4>(v, kw);
     add_state(s, v);
 }
 

@@ -13,6 +13,7 @@
 // The device side is behind a small backend interface so that the queue,
 // admission and retirement logic also runs on the CPU in tests (host
 // backend: the "device" is host memory and verification is a callback).
+#include <emmintrin.h>
 #include <algorithm>
 #include <atomic>
 #include <chrono>
@@ -280,6 +281,34 @@ double now_s()
     return duration<double>(steady_clock::now().time_since_epoch()).count();
 }
 
+// Copy of a request's array into staging (dst 16-byte aligned).  The copy's
+// next reader is the device, so large ones go past the caches with streaming
+// stores: an ordinary store first reads the line it is about to overwrite
+// (48 requests of 43 MB in all from one submitting thread 2.05-2.14 -> 1.81-1.94
+// ms).  The fence orders them before the request is handed to the server.
+constexpr size_t kStreamCopyMin = 64u << 10;
+
+void stage_copy(uint8_t *dst, const uint8_t *src, size_t n)
+{
+    if (n < kStreamCopyMin || !aligned(dst, 16)) {
+        memcpy(dst, src, n);
+        return;
+    }
+    size_t i = 0;
+    for (; i + 64 <= n; i += 64) {
+        const __m128i *p = reinterpret_cast<const __m128i *>(src + i);
+        __m128i *q = reinterpret_cast<__m128i *>(dst + i);
+        const __m128i a = _mm_loadu_si128(p), b = _mm_loadu_si128(p + 1), c = _mm_loadu_si128(p + 2),
+                      d = _mm_loadu_si128(p + 3);
+        _mm_stream_si128(q, a);
+        _mm_stream_si128(q + 1, b);
+        _mm_stream_si128(q + 2, c);
+        _mm_stream_si128(q + 3, d);
+    }
+    memcpy(dst + i, src + i, n - i);
+    _mm_sfence();
+}
+
 // A client call inside the engine: counted under the lock so that
 // ace_stream_destroy frees nothing while one is still running.
 struct InCall {
@@ -439,8 +468,10 @@ bool admit(ace_stream *s)
             bk.d_count_out = reinterpret_cast<uint64_t *>(fake);
             bk.n_tx = r->n;
         }
+        // (sorted beyond one wave per SIMD, as an open call is)
         vflags = m_tx >= tn.binned_min_tx ? (ACE_BUCKETED | (tn.auto_persistent ? ACE_PERSISTENT : 0u))
-                                          : ACE_ORDERED;
+                 : m_tx > 256ull * (unsigned)cu_count() ? ACE_BUCKETED
+                                                        : ACE_ORDERED;
         const size_t ws = align_up(s->be->ws_size(blocks.data(), (uint32_t)m, vflags), 256);
         arena_bytes = in_total + align_up(out_total, 256) + ws;
         if (ws && s->arena_alloc.alloc(arena_bytes, arena_off)) break;
@@ -735,9 +766,9 @@ ACE_API int ace_verify_stream(ace_stream *s, const uint8_t *h_msg, const uint64_
     uint64_t *off = reinterpret_cast<uint64_t *>(st + lay.off_off);
     if (n_tx) {
         for (uint64_t i = 0; i <= n_tx; ++i) off[i] = h_off[i] - lo;
-        memcpy(st + lay.off_id, h_id, 4 * n_tx);
-        memcpy(st + lay.off_tag, h_tag, 32 * n_tx);
-        if (msg_bytes) memcpy(st + lay.off_msg, h_msg + lo, msg_bytes);
+        stage_copy(st + lay.off_id, reinterpret_cast<const uint8_t *>(h_id), 4 * n_tx);
+        stage_copy(st + lay.off_tag, h_tag, 32 * n_tx);
+        if (msg_bytes) stage_copy(st + lay.off_msg, h_msg + lo, msg_bytes);
     } else {
         off[0] = 0;
     }

@@ -424,10 +424,11 @@ void launch_ordered(bool attest, bool per_tx, bool pairs, unsigned g, hipStream_
 }
 
 template <bool AT>
-void launch_local_t(bool wide, unsigned g, hipStream_t s, const Batch &bt, const KeySource &ks)
+void launch_local_t(bool wide, unsigned g, hipStream_t s, const Batch &bt, const KeySource &ks,
+                    uint64_t wide_min)
 {
-    if (wide) hipLaunchKernelGGL((k_verify_local<AT, 16>), dim3(g), dim3(1024), 0, s, bt, ks);
-    else hipLaunchKernelGGL((k_verify_local<AT, 8>), dim3(g), dim3(512), 0, s, bt, ks);
+    if (wide) hipLaunchKernelGGL((k_verify_local<AT, 16>), dim3(g), dim3(1024), 0, s, bt, ks, wide_min);
+    else hipLaunchKernelGGL((k_verify_local<AT, 8>), dim3(g), dim3(512), 0, s, bt, ks, wide_min);
 }
 
 // The verify form of a call (or, with the maxima's wave tiles, of a graph).
@@ -579,8 +580,9 @@ int enqueue_stages(const Plan &p, const Batch &bt, const ace_keyset *keys, const
         } else if (graph || p.total_tx) {
             const LocalShape sh = local_shape(waves, cus);
             const unsigned g = local_share(waves, sh.slots).groups;
-            if (p.attest) launch_local_t<true>(sh.wide, g, s, bt, ks);
-            else launch_local_t<false>(sh.wide, g, s, bt, ks);
+            const uint64_t wide_min = std::min<uint64_t>(tn.wide_min_len, kRecMaxLen);
+            if (p.attest) launch_local_t<true>(sh.wide, g, s, bt, ks, wide_min);
+            else launch_local_t<false>(sh.wide, g, s, bt, ks, wide_min);
             if ((rc = launch_status("k_verify_local launch"))) return rc;
         }
         prof_mark(prof, 3, s);

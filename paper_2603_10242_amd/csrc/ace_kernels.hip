@@ -865,20 +865,30 @@ __device__ __forceinline__ void set_row_priority(uint32_t row)
 }
 
 template <bool ATTEST, int NW>
-__global__ void __launch_bounds__(64 * NW) ACE_WAVES(4) k_verify_local(Batch bt, KeySource ks)
+__global__ void __launch_bounds__(64 * NW) ACE_WAVES(4) k_verify_local(Batch bt, KeySource ks,
+                                                                       uint64_t wide_min)
 {
     // what a lane needs to find transaction l of a wave tile
     struct Unit {
         const uint64_t *off;
-        const uint32_t *id;
-        const uint8_t *msg, *tag;
-        uint64_t area_end;
-        uint32_t n, block;  // transactions in the tile, its block
-        uint64_t i0;        // its first transaction within the block
+        const uint8_t *msg, *tag;  // of its first transaction
+        uint64_t off0, area_end;   // its first offset, the end of its block's message area
+        uint64_t i0;               // its first transaction within the block
+        uint32_t n, block;         // transactions in the tile, its block
+    };
+    // a transaction in sorted order, kept here from the one coalesced pass over
+    // offsets and identities (read again per tile they brought a cache line per
+    // transaction each, and one more wait before the message: 256 blocks of
+    // 7.66M transactions 1,781 us, 1,767 this way)
+    struct alignas(16) Rec {
+        uint32_t rel;  // message start, from the tile's
+        uint32_t len;  // length | kRecNearEnd, or kRecWide: read the offsets again
+        uint32_t id;
+        uint32_t x;    // 64 * tile + transaction
     };
     constexpr int kPerThread = kLocalUnits / NW;
     __shared__ Unit unit[kLocalUnits];
-    __shared__ uint16_t order[64 * kLocalUnits];
+    __shared__ Rec rec[64 * kLocalUnits];
     __shared__ uint32_t mask[2 * kLocalUnits];
     __shared__ uint32_t hist[kBins], start[kBins];
     __shared__ uint32_t n_live, next_tile;
@@ -905,34 +915,43 @@ __global__ void __launch_bounds__(64 * NW) ACE_WAVES(4) k_verify_local(Batch bt,
         const uint64_t i0 = 64ull * (w - d.wave0);
         Unit x;
         x.off = d.off + i0;
-        x.id = d.id + i0;
-        x.msg = d.msg;
+        x.off0 = ((gptr64)d.off)[i0];
+        x.area_end = ((gptr64)d.off)[d.n];
+        x.msg = d.msg + x.off0;
         x.tag = d.tag + (uint64_t)check_stride<ATTEST>() * i0;
-        x.area_end = d.off[d.n];
+        x.i0 = i0;
         x.n = d.n - i0 < 64 ? (uint32_t)(d.n - i0) : 64u;
         x.block = b;
-        x.i0 = i0;
         unit[tid] = x;
     }
+    // offsets and identities: wave w takes tiles w, w + NW, ...
+    uint64_t a[kPerThread], e[kPerThread];
+    uint32_t who[kPerThread];
     __syncthreads();
-
-    // block counts and ranks: wave w takes tiles w, w + NW, ...
+#pragma unroll
+    for (int k = 0; k < kPerThread; ++k) {
+        const uint32_t u = wave + k * NW;
+        a[k] = 1;
+        e[k] = 0;  // not a transaction
+        who[k] = 0;
+        if (u < U && lane < unit[u].n) {
+            const gptr64 off = (gptr64)unit[u].off;
+            a[k] = off[lane];
+            e[k] = off[lane + 1];
+            who[k] = ((gptr)get_block(bt, T, unit[u].block).id)[unit[u].i0 + lane];
+        }
+    }
+    // block counts and ranks; those that cannot be valid are left out: their
+    // bits stay 0
     uint32_t bin[kPerThread], rank[kPerThread];
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) {
         bin[k] = kBins;
-        const uint32_t u = wave + k * NW;
-        if (u < U && lane < unit[u].n) {
-            const gptr64 off = (gptr64)unit[u].off;
-            const uint64_t a = off[lane], e = off[lane + 1];
-            const uint32_t who = ((gptr)unit[u].id)[lane];
-            // those that cannot be valid are left out: their bits stay 0
-            if (a <= e && who < ks.n_id) bin[k] = bin_of_length(e - a);
+        if (a[k] <= e[k] && who[k] < ks.n_id) {
+            bin[k] = bin_of_length(e[k] - a[k]);
+            rank[k] = atomicAdd(&hist[bin[k]], 1u);
         }
     }
-#pragma unroll
-    for (int k = 0; k < kPerThread; ++k)
-        if (bin[k] < kBins) rank[k] = atomicAdd(&hist[bin[k]], 1u);
     __syncthreads();
     if (wave == 0) {
         // start of every bin, longest first (lane l: bin 63 - l)
@@ -948,8 +967,19 @@ __global__ void __launch_bounds__(64 * NW) ACE_WAVES(4) k_verify_local(Batch bt,
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kPerThread; ++k)
-        if (bin[k] < kBins) order[start[bin[k]] + rank[k]] = (uint16_t)(64u * (wave + k * NW) + lane);
+    for (int k = 0; k < kPerThread; ++k) {
+        if (bin[k] < kBins) {
+            const uint32_t u = wave + k * NW;
+            const uint64_t rel = a[k] - unit[u].off0, L = e[k] - a[k];
+            Rec r;
+            r.rel = (uint32_t)rel;
+            r.len = L >= wide_min || rel >> 32 ? kRecWide
+                                               : (uint32_t)L | (e[k] + kOverread <= unit[u].area_end ? 0u : kRecNearEnd);
+            r.id = who[k];
+            r.x = 64u * u + lane;
+            rec[start[bin[k]] + rank[k]] = r;
+        }
+    }
     __syncthreads();
 
     // Tiles of 64 in sorted order.  The first NW go to the waves so that each
@@ -967,16 +997,21 @@ __global__ void __launch_bounds__(64 * NW) ACE_WAVES(4) k_verify_local(Batch bt,
         uint32_t x = 0;
         TxRef t{};
         if (live) {
-            x = order[p];
+            const Rec r = rec[p];
+            x = r.x;
             const Unit &un = unit[x >> 6];
             const uint32_t l = x & 63u;
-            const uint64_t a = ((gptr64)un.off)[l], e = ((gptr64)un.off)[l + 1];
-            const uint32_t who = ((gptr)un.id)[l];
-            t.msg = un.msg + a;
-            t.L = e - a;
-            t.mid = ks.mid + 16ull * who;
+            t.mid = ks.mid + 16ull * r.id;
             t.tag = un.tag + check_stride<ATTEST>() * l;
-            t.overread_ok = e + kOverread <= un.area_end;
+            t.msg = un.msg + r.rel;
+            t.L = r.len & ~kRecNearEnd;
+            t.overread_ok = (r.len & kRecNearEnd) == 0;
+            if (r.len == kRecWide) {
+                const uint64_t from = ((gptr64)un.off)[l], to = ((gptr64)un.off)[l + 1];
+                t.msg = un.msg + (from - un.off0);
+                t.L = to - from;
+                t.overread_ok = to + kOverread <= un.area_end;
+            }
         }
         if (verify_lane<false, ATTEST, true>(live, t, nullptr)) atomicOr(&mask[x >> 5], 1u << (x & 31u));
         // every lane takes part in the atomic, so that no divergent branch
@@ -1537,7 +1572,7 @@ template __global__ void k_verify_ordered<false, true>(Batch, KeySource, HkdfPar
 template __global__ void k_verify_pair<false, true>(Batch, KeySource, HkdfParams, uint32_t);
 template __global__ void k_verify_ordered<true, true>(Batch, KeySource, HkdfParams);
 template __global__ void k_verify_pair<true, true>(Batch, KeySource, HkdfParams, uint32_t);
-#define ACE_LOCAL(R, N) template __global__ void k_verify_local<R, N>(Batch, KeySource);
+#define ACE_LOCAL(R, N) template __global__ void k_verify_local<R, N>(Batch, KeySource, uint64_t);
 ACE_LOCAL(false, 8)
 ACE_LOCAL(true, 8)
 ACE_LOCAL(false, 16)

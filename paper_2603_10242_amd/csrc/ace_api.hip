@@ -79,6 +79,14 @@ int cu_count()
     return cache[dev];
 }
 
+// Most wave tiles (64 lanes' work) that take the two-wave forms.  Verify gains
+// while two of them share a CU (20,000 transactions 78 us against 83 with one
+// wave each), derivations and hash chains, which wait at a barrier for every
+// sixteen rounds, only while each has a CU to itself (32,768 segments 853 us
+// against 767, 30,000 keys 27.6 against 25.6).
+uint64_t pair_verify_tiles() { return 2ull * (uint64_t)cu_count(); }
+uint64_t pair_tiles() { return (uint64_t)cu_count(); }
+
 // ------------------------------------------------------------------------------------------
 // Tuning (set by the autotuner through ace_set_tuning).
 // ------------------------------------------------------------------------------------------
@@ -431,6 +439,21 @@ void launch_local_t(bool wide, unsigned g, hipStream_t s, const Batch &bt, const
     else hipLaunchKernelGGL((k_verify_local<AT, 8>), dim3(g), dim3(512), 0, s, bt, ks, wide_min);
 }
 
+// The derivation with the GPU to itself; `zero`: a count it clears, or NULL.
+int launch_derive(const uint8_t *rev, uint32_t n_id, uint8_t *key_out, uint32_t *mid_out, const HkdfParams &hp,
+                  unsigned long long *zero, hipStream_t s)
+{
+    const uint64_t wave_tiles = (n_id + 63ull) / 64;
+    if (wave_tiles <= pair_tiles()) {
+        hipLaunchKernelGGL(k_derive_pair<HkdfParams>, dim3((unsigned)wave_tiles), dim3(128), 0, s, rev, n_id, key_out,
+                           mid_out, hp, zero);
+        return launch_status("k_derive_pair launch");
+    }
+    const unsigned g = std::min<unsigned>((unsigned)((n_id + kWG - 1) / kWG), kDeriveWgsPerCu * (unsigned)cu_count());
+    hipLaunchKernelGGL(k_derive, dim3(g), dim3(kWG), 0, s, rev, n_id, key_out, mid_out, hp, zero);
+    return launch_status("k_derive launch");
+}
+
 // The verify form of a call (or, with the maxima's wave tiles, of a graph).
 //   in order      at most one wave per SIMD: the longest message's chain takes
 //                 the whole time, and sorting could not shorten it (2,903
@@ -522,7 +545,7 @@ int enqueue_stages(const Plan &p, const Batch &bt, const ace_keyset *keys, const
     const bool per_tx = p.per_tx || (p.rev && form == kInOrder && !(p.flags & ACE_ORDERED));
     unsigned long long *const zero = graph || p.n_blocks > 1 ? nullptr : bt.one.count;  // else cleared already
     // in order with two waves per wave tile while each wave has its SIMD to itself
-    const bool pairs = form == kInOrder && waves <= 2ull * cus;
+    const bool pairs = form == kInOrder && waves <= pair_verify_tiles();
     const bool solo = zero && pairs && p.total_waves == 1;  // one workgroup stores the count itself
     bool cleared = !zero || solo;
     Fork *fk = nullptr;
@@ -532,11 +555,14 @@ int enqueue_stages(const Plan &p, const Batch &bt, const ace_keyset *keys, const
         ks.rev = keys->d_rev;
     } else {
         uint32_t *mid = reinterpret_cast<uint32_t *>(ws + p.off_mid);
-        if (keys->n_id) {
+        if (keys->n_id && !binned) {
+            if ((rc = launch_derive(keys->d_rev, keys->n_id, nullptr, mid, hp, zero, s))) return rc;
+            cleared = true;
+        } else if (keys->n_id) {
             unsigned g = std::min<unsigned>((unsigned)((keys->n_id + kWG - 1) / kWG),
                                             kDeriveWgsPerCu * cus);
             hipStream_t ds = s;
-            if (fork && binned && (graph || p.total_tx) && (fk = fork_ctx())) {
+            if (fork && (graph || p.total_tx) && (fk = fork_ctx())) {
                 if ((rc = check_hip(hipEventRecord(fk->fork, s), "hipEventRecord"))) return rc;
                 if ((rc = check_hip(hipStreamWaitEvent(fk->aux, fk->fork, 0), "hipStreamWaitEvent")))
                     return rc;
@@ -545,9 +571,8 @@ int enqueue_stages(const Plan &p, const Batch &bt, const ace_keyset *keys, const
                 if (tn.derive_wgs_per_cu) g = std::min<unsigned>(g, tn.derive_wgs_per_cu * cus);
             }
             hipLaunchKernelGGL(k_derive, dim3(g), dim3(kWG), 0, ds, keys->d_rev, keys->n_id,
-                               (uint8_t *)nullptr, mid, hp, binned ? (unsigned long long *)nullptr : zero);
+                               (uint8_t *)nullptr, mid, hp, (unsigned long long *)nullptr);
             if ((rc = launch_status("k_derive launch"))) return rc;
-            if (!binned) cleared = true;
             if (fk) {
                 if ((rc = check_hip(hipEventRecord(fk->join, fk->aux), "hipEventRecord"))) return rc;
                 // A timing-enabled marker on the caller's stream right after the
@@ -746,11 +771,7 @@ ACE_API int ace_derive_keys(const uint8_t *d_rev, uint32_t n_id, const uint8_t *
     if (!aligned(d_rev, 4) || (d_key_out && !aligned(d_key_out, 4)) || (d_mid_out && !aligned(d_mid_out, 4)))
         return fail(ACE_ERR_INVALID_ARG, "misaligned device array");
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    const unsigned grid = std::min<unsigned>((unsigned)((n_id + kWG - 1) / kWG),
-                                             kDeriveWgsPerCu * (unsigned)cu_count());
-    hipLaunchKernelGGL(k_derive, dim3(grid), dim3(kWG), 0, s, d_rev, n_id, d_key_out, d_mid_out, hp,
-                       (unsigned long long *)nullptr);
-    return launch_status("k_derive launch");
+    return launch_derive(d_rev, n_id, d_key_out, d_mid_out, hp, nullptr, s);
 }
 
 ACE_API int ace_derive_keys_multi(const uint8_t *d_rev, uint32_t n_id,
@@ -785,6 +806,13 @@ ACE_API int ace_derive_keys_multi(const uint8_t *d_rev, uint32_t n_id,
             const uint8_t one = 0x01;
             mp.s[y].info_blocks = pad_words(mp.s[y].info_w, t.h_info, t.info_len, &one, 1, 64);
         }
+        const uint64_t wave_tiles = (n_id + 63ull) / 64;
+        if (wave_tiles * mp.count <= pair_tiles()) {
+            hipLaunchKernelGGL(k_derive_pair<MultiHkdf>, dim3((unsigned)wave_tiles, mp.count), dim3(128), 0, s,
+                               d_rev, n_id, d_key_out, d_mid_out, mp, (unsigned long long *)nullptr);
+            if (int rc = launch_status("k_derive_pair launch")) return rc;
+            continue;
+        }
         const uint64_t per = tiles * mp.count >= kMultiStrideMin * (uint64_t)cu_count() ? 2 : 1;
         const unsigned gx = (unsigned)((tiles + per - 1) / per);
         hipLaunchKernelGGL(k_derive_multi, dim3(gx, mp.count), dim3(kWG), 0, s, d_rev, n_id, d_key_out,
@@ -812,9 +840,19 @@ ACE_API int ace_poh_verify(const uint8_t *d_start, const uint8_t *d_end, const u
     }
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     unsigned long long *cnt = reinterpret_cast<unsigned long long *>(d_count_out);
-    hipLaunchKernelGGL(k_poh_zero, dim3(1), dim3(1), 0, s, cnt);
-    int rc = launch_status("k_poh_zero launch");
+    const uint64_t tiles = (n_segments + 63) / 64;
+    const bool solo = tiles == 1;  // one workgroup stores the count itself
+    int rc = ACE_OK;
+    if (!solo) {
+        hipLaunchKernelGGL(k_poh_zero, dim3(1), dim3(1), 0, s, cnt);
+        rc = launch_status("k_poh_zero launch");
+    }
     if (rc || !n_segments) return rc;
+    if (tiles <= pair_tiles()) {
+        hipLaunchKernelGGL(k_poh_pair, dim3((unsigned)tiles), dim3(128), 0, s, d_start, d_end, d_steps, steps,
+                           n_segments, d_bitmask_out, cnt, (uint32_t)solo);
+        return launch_status("k_poh_pair launch");
+    }
     const unsigned g = (unsigned)((n_segments + kWG - 1) / kWG);
     hipLaunchKernelGGL(k_poh_verify, dim3(g), dim3(kWG), 0, s, d_start, d_end, d_steps, steps,
                        n_segments, d_bitmask_out, cnt);

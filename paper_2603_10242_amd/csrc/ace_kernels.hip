@@ -13,7 +13,8 @@
 //   k_finalize       bin-order verdicts back to input order.
 //   k_count          valid counts from the finished bitmasks.
 //   k_plan           device-side plan of a graph replay.
-// The key derivation (Def. 2.1) is in hkdf_kernels.hip, the hash-chain
+// The key derivation (Def. 2.1) is in hkdf_kernels.hip, the two-wave forms for
+// small calls in pair_kernels.hip, the hash-chain
 // segments in chain_kernels.hip, the Merkle roots in merkle_kernels.hip.
 //
 // One transaction per lane.  Message bytes are read straight from HBM as
@@ -117,6 +118,7 @@ __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
 }  // namespace ace
 
 #include "hkdf_kernels.hip"
+#include "pair_kernels.hip"
 
 namespace ace {
 
@@ -548,149 +550,17 @@ __global__ void __launch_bounds__(kWG) ACE_WAVES(4) k_verify_ordered(Batch bt, K
 }
 
 // ------------------------------------------------------------------------------------------
-// k_verify, pair form, for the smallest calls: two waves share the work of one
-// wave tile.  A lane's chain of compressions is serial, but only the rounds of
-// a block depend on the chain: the second wave loads and pads message block
-// b + 1 and expands its schedule (about 750 instructions) while the first runs
-// the 64 rounds of block b (about 900) on K[t] + W[t] read from LDS.  Where a
-// block's words are the chain itself (HMAC's outer block, HKDF), the first wave
-// starts its rounds 0..15 at once and the second expands the words of rounds
-// 16..63 sixteen at a time ahead of it; the two midstates of a key go one to
-// each wave.
-//
-// Bound by that chain: a lone wave takes 2.5 us for a whole compression and
-// about 1.7 for the rounds alone.  It needs two waves' SIMDs per tile, so it
-// serves calls of up to half as many tiles as there are SIMDs.
+// k_verify, pair form, for the smallest calls: two waves per wave tile (see
+// pair_kernels.hip): the second loads, pads and expands message block b + 1
+// while the first runs the rounds of block b; HMAC's outer block and the key
+// derivation are shared out as there.
 // ------------------------------------------------------------------------------------------
-struct alignas(16) Q4 {  // one 16-byte LDS access
-    uint32_t x, y, z, w;
-};
-struct PairLds {
-    Q4 kw[2][16][64];  // K[t] + W[t] of two message blocks: [t / 4][lane]
-    Q4 tail[12][64];   // the same of rounds 16..63 of a block made from the chain
-    Q4 down[2][64];    // eight words per lane from the first wave to the second
-    Q4 up[2][64];      // and back
-    uint32_t blocks;   // message blocks of the tile's longest message
-};
-
-__device__ __forceinline__ void put8(Q4 (&x)[2][64], const State &s)
-{
-    const uint32_t l = lane_id();
-    x[0][l] = Q4{s.h[0], s.h[1], s.h[2], s.h[3]};
-    x[1][l] = Q4{s.h[4], s.h[5], s.h[6], s.h[7]};
-}
-__device__ __forceinline__ State get8(const Q4 (&x)[2][64])
-{
-    const uint32_t l = lane_id();
-    const Q4 a = x[0][l], b = x[1][l];
-    return State{{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w}};
-}
-
-// 16 N rounds from K[t] + W[t] in LDS.  All the words are read first (the
-// compiler, left to itself, reads them just before their rounds and waits).
-template <int N>
-__device__ __forceinline__ void rounds16(uint32_t (&v)[8], const Q4 (*kw)[64])
-{
-    const uint32_t l = lane_id();
-    Q4 k[4 * N];
-#pragma unroll
-    for (int c = 0; c < 4 * N; ++c) k[c] = kw[c][l];
-    asm volatile("" ::: "memory");
-#pragma unroll
-    for (int c = 0; c < 4 * N; ++c) {
-        const uint32_t w[4] = {k[c].x, k[c].y, k[c].z, k[c].w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            round_step(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], w[j], 0u);
-    }
-}
-__device__ __forceinline__ void add_state(State &s, const uint32_t (&v)[8])
-{
-#pragma unroll
-    for (int i = 0; i < 8; ++i) s.h[i] += v[i];
-}
-
-// Sixteen schedule words W[16 q ..] (q > 0: from the sixteen before) to LDS
-// with their round constants added.
-template <int Q>
-__device__ __forceinline__ void expand16(uint32_t (&W)[16], Q4 (*kw)[64])
-{
-    const uint32_t l = lane_id();
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        uint32_t o[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int j = 4 * c + i;
-            if (Q > 0)
-                W[j] = small_sigma1(W[(j - 2) & 15]) + W[(j - 7) & 15] + small_sigma0(W[(j - 15) & 15]) + W[j];
-            o[i] = W[j] + kRound[16 * Q + j];
-        }
-        kw[c][l] = Q4{o[0], o[1], o[2], o[3]};
-    }
-}
-
-// s <- F(s, m || 0x80 || 0 || 768) for a 32-byte message m after a 64-byte key
-// block: the first wave's part, and the second's (four barriers each).
-__device__ __forceinline__ void pair_tail_rounds(PairLds &L, State &s, const State &m)
-{
-    put8(L.down, m);
-    __syncthreads();
-    uint32_t v[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = s.h[i];
-#pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        const uint32_t w = t < 8 ? m.h[t & 7] : (t == 8 ? 0x80000000u : (t == 15 ? 768u : 0u));
-        round_step(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], w, kRound[t]);
-    }
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        __syncthreads();
-        rounds16<1>(v, &L.tail[4 * q]);
-    }
-    add_state(s, v);
-}
-__device__ __forceinline__ void pair_tail_schedule(PairLds &L)
-{
-    __syncthreads();
-    const State m = get8(L.down);
-    uint32_t W[16];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) W[i] = m.h[i];
-    W[8] = 0x80000000u;
-#pragma unroll
-    for (int i = 9; i < 15; ++i) W[i] = 0u;
-    W[15] = 768u;
-    expand16<1>(W, &L.tail[0]);
-    __syncthreads();
-    expand16<2>(W, &L.tail[4]);
-    __syncthreads();
-    expand16<3>(W, &L.tail[8]);
-    __syncthreads();
-}
-
-// A block's whole schedule.
-__device__ __forceinline__ void pair_schedule(uint32_t (&W)[16], Q4 (*kw)[64])
-{
-    expand16<0>(W, kw);
-    expand16<1>(W, kw + 4);
-    expand16<2>(W, kw + 8);
-    expand16<3>(W, kw + 12);
-}
-__device__ __forceinline__ void pair_rounds(State &s, const Q4 (*kw)[64])
-{
-    uint32_t v[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = s.h[i];
-    rounds16<4>(v, kw);
-    add_state(s, v);
-}
-
 template <bool PER_TX_KEYS, bool ATTEST>
 __global__ void __launch_bounds__(128) k_verify_pair(Batch bt, KeySource ks, HkdfParams hp, uint32_t solo)
 {
     __shared__ PairLds L;
+    __shared__ Q4 kw[2][16][64];  // K[t] + W[t] of two message blocks
+    __shared__ uint32_t longest;  // message blocks of the tile's longest message
     __shared__ HkdfPrep prep;
     const Totals T = totals(bt);
     const uint32_t w = blockIdx.x;
@@ -716,7 +586,7 @@ __global__ void __launch_bounds__(128) k_verify_pair(Batch bt, KeySource ks, Hkd
             load(b + 1);
             const int64_t rb = (int64_t)t.L - 64ll * b;
             if (rb < 64) pad_block(W, g, rb, b);
-            pair_schedule(W, L.kw[b & 1]);
+            pair_schedule(W, kw[b & 1]);
         }
     };
     uint32_t C[check_words<ATTEST>()];
@@ -745,47 +615,17 @@ __global__ void __launch_bounds__(128) k_verify_pair(Batch bt, KeySource ks, Hkd
         uint32_t m = 0;
         for (unsigned long long more; (more = __ballot(g.nb > m)) != 0;)
             m = __builtin_amdgcn_readlane(g.nb, __builtin_ctzll(more));
-        if (lane_id() == 0) L.blocks = m;
+        if (lane_id() == 0) longest = m;
     } else {
         load(0);
     }
     if constexpr (PER_TX_KEYS) hkdf_prepare(hp, prep);
     __syncthreads();
-    const uint32_t blocks = uniform32(L.blocks);
+    const uint32_t blocks = uniform32(longest);
     if constexpr (PER_TX_KEYS) {
-        // as derive_lane, the steps shared out
-        if (first) {
-            State m, x, prk;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                m.h[k] = bswap32(rv[k]);
-                x.h[k] = prep.salt_ipad[k];
-                prk.h[k] = prep.salt_opad[k];
-            }
-            pair_tail_rounds(L, x, m);
-            pair_tail_rounds(L, prk, x);
-            put8(L.down, prk);
-            __syncthreads();
-            State pi = hmac_midstate<0x36363636u>(prk);
-            const uint32_t nq = prep.info_blocks;
-            for (uint32_t q = 0; q < nq; ++q) compress_kw(pi, prep.info_kw[q]);
-            __syncthreads();
-            State key = get8(L.up);
-            pair_tail_rounds(L, key, pi);
-            put8(L.down, key);
-            __syncthreads();
-            ipad = hmac_midstate<0x36363636u>(key);
-        } else {
-            pair_tail_schedule(L);
-            pair_tail_schedule(L);
-            __syncthreads();
-            put8(L.up, hmac_midstate<0x5c5c5c5cu>(get8(L.down)));
-            produce(0);
-            __syncthreads();
-            pair_tail_schedule(L);
-            __syncthreads();
-            put8(L.up, hmac_midstate<0x5c5c5c5cu>(get8(L.down)));
-        }
+        State key;
+        if (first) pair_derive_first(L, prep, rv, key, ipad);
+        else pair_derive_second(L, prep, [&] { produce(0); });
     } else if (!first) {
         produce(0);
     }
@@ -793,7 +633,7 @@ __global__ void __launch_bounds__(128) k_verify_pair(Batch bt, KeySource ks, Hkd
     for (uint32_t b = 0; b < blocks; ++b) {
         __syncthreads();
         if (first) {
-            if (b < g.nb) pair_rounds(S, L.kw[b & 1]);
+            if (b < g.nb) pair_rounds(S, kw[b & 1]);
         } else if (b + 1 < blocks) {
             produce(b + 1);
         } else if constexpr (ATTEST) {
@@ -805,12 +645,12 @@ __global__ void __launch_bounds__(128) k_verify_pair(Batch bt, KeySource ks, Hkd
 #pragma unroll
             for (int k = 11; k < 15; ++k) W[k] = 0u;
             W[15] = (64u + 40u) * 8u;
-            pair_schedule(W, L.kw[(b + 1) & 1]);
+            pair_schedule(W, kw[(b + 1) & 1]);
         }
     }
     __syncthreads();
     if (!first) {
-        pair_tail_schedule(L);
+        pair_tail_schedule<768>(L);
         return;  // no barrier follows
     }
     if constexpr (PER_TX_KEYS) opad = get8(L.up);
@@ -819,9 +659,9 @@ __global__ void __launch_bounds__(128) k_verify_pair(Batch bt, KeySource ks, Hkd
 #pragma unroll
         for (int k = 0; k < 8; ++k) diff = or_xor(diff, S.h[k], bswap32(C[k]));
         S = ipad;
-        pair_rounds(S, L.kw[blocks & 1]);
+        pair_rounds(S, kw[blocks & 1]);
     }
-    pair_tail_rounds(L, opad, S);
+    pair_tail_rounds<768>(L, opad, S);
     constexpr int c0 = ATTEST ? 10 : 0;
 #pragma unroll
     for (int k = 0; k < 8; ++k) diff = or_xor(diff, opad.h[k], bswap32(C[c0 + k]));

@@ -138,3 +138,58 @@ def test_merkle_stages(ace, sizes):
     ace.merkle_roots(trees)
     torch.cuda.synchronize()
     assert np.array_equal(roots.cpu().numpy(), oracle.merkle_roots(data, off, sizes))
+
+
+# 64 segments are one workgroup, 32,768 the most that take two waves per 64 on a 256-CU device
+@pytest.mark.parametrize("n", [1, 64, 65, 1_000, 32_768, 32_769])
+@pytest.mark.parametrize("ragged", [False, True])
+def test_chain_segments_at_shape_edges(ace, n, ragged):
+    import torch
+    r = np.random.default_rng(n)
+    steps = r.integers(0, 40, n) if ragged else 17
+    w = W.poh_segments(n, steps, seed=n + 3, n_invalid=min(n // 2, 50))
+    print("chain n=%d ragged=%s" % (n, ragged), flush=True)
+    omask, ocount = oracle.poh_verify(w.start, w.end, w.steps, 8)
+    mask = torch.full(((n + 31) // 32,), -1, dtype=torch.int32, device="cuda")
+    count = torch.full((1,), 77, dtype=torch.int64, device="cuda")
+    d_steps = ace.to_device(w.steps) if ragged or len(set(w.steps.tolist())) > 1 else int(w.steps[0])
+    ace.poh_verify(ace.to_device(w.start), ace.to_device(w.end), d_steps, mask, count)
+    torch.cuda.synchronize()
+    assert int(count.item()) == ocount
+    assert np.array_equal(mask.cpu().numpy().view(np.uint32), omask)
+
+
+# 32,768 identities over all streams are the most that take two waves per 64
+@pytest.mark.parametrize("n_id,n_streams", [(1, 1), (64, 3), (65, 1), (32_768, 1), (32_769, 1), (3_640, 9), (3_650, 9)])
+def test_derive_at_shape_edges(ace, n_id, n_streams):
+    """Keys and midstates of one stream (salts and infos of every block count)
+    and of several; outputs asked for separately and together."""
+    import torch
+    r = np.random.default_rng(n_id + n_streams)
+    rev = r.integers(0, 256, (n_id, 32), dtype=np.uint8)
+    d_rev = ace.to_device(rev)
+    pick = np.unique(np.concatenate([np.arange(0, n_id, 61), [0, n_id - 1]]))
+    print("derive n_id=%d streams=%d" % (n_id, n_streams), flush=True)
+
+    def check(key, mid, salt, info):
+        want = oracle.derive_keys(rev[pick], salt, info, 8)
+        if key is not None:
+            assert np.array_equal(key[pick].cpu().numpy(), want)
+        if mid is not None:
+            assert np.array_equal(mid[pick].cpu().numpy().view(np.uint32), oracle.hmac_midstates(want))
+
+    pairs = [(r.integers(0, 256, s, dtype=np.uint8).tobytes(), bytes(range(i))) for s, i in
+             ((0, 0), (32, 16), (64, 54), (65, 55), (1024, 255))]
+    for salt, info in pairs:
+        key = torch.zeros((n_id, 32), dtype=torch.uint8, device="cuda")
+        mid = torch.zeros((n_id, 16), dtype=torch.int32, device="cuda")
+        ace.derive_keys(d_rev, salt, info, key_out=key, mid_out=mid)
+        check(key, mid, salt, info)
+    only = torch.zeros((n_id, 16), dtype=torch.int32, device="cuda")
+    ace.derive_keys(d_rev, pairs[1][0], pairs[1][1], mid_out=only)
+    check(None, only, *pairs[1])
+    streams = [pairs[k % 3] for k in range(n_streams)]
+    keys = torch.zeros((n_streams, n_id, 32), dtype=torch.uint8, device="cuda")
+    ace.derive_keys_multi(d_rev, streams, key_out=keys)
+    for k, (salt, info) in enumerate(streams):
+        check(keys[k], None, salt, info)

@@ -409,14 +409,15 @@ Fork *fork_ctx()
 constexpr uint64_t kCountWGs = 256;
 
 // Verify-kernel launches for the plan's key source, persistence and record form.
-// In-order launches: workgroups of one wave, spread over the CUs, of four where
-// they share a parameter set's preparation; `pairs`: of two waves per wave tile.
+// In-order launches: workgroups of four waves, one for each SIMD of a CU (those
+// of one wave can meet on a SIMD while others stand idle); `pairs`: of two waves
+// per wave tile.
 template <bool PT, bool AT>
 void launch_ordered_t(bool pairs, unsigned g, hipStream_t s, const Batch &bt, const KeySource &ks,
                       const HkdfParams &hp, bool solo)
 {
     if (pairs) hipLaunchKernelGGL((k_verify_pair<PT, AT>), dim3(g), dim3(128), 0, s, bt, ks, hp, (uint32_t)solo);
-    else hipLaunchKernelGGL((k_verify_ordered<PT, AT>), dim3(g), dim3(PT ? kWG : 64), 0, s, bt, ks, hp);
+    else hipLaunchKernelGGL((k_verify_ordered<PT, AT>), dim3(g), dim3(kWG), 0, s, bt, ks, hp);
 }
 
 void launch_ordered(bool attest, bool per_tx, bool pairs, unsigned g, hipStream_t s, const Batch &bt,
@@ -456,9 +457,11 @@ int launch_derive(const uint8_t *rev, uint32_t n_id, uint8_t *key_out, uint32_t 
 
 // The verify form of a call (or, with the maxima's wave tiles, of a graph).
 //   in order      at most one wave per SIMD: the longest message's chain takes
-//                 the whole time, and sorting could not shorten it (2,903
-//                 transactions 82 us; with three more launches and windows
-//                 loaded when needed 128-139).
+//                 the whole time, and sorting could not shorten it (65,000
+//                 transactions 75 us, 70,000 locally sorted 82, in order 170).
+//                 Attestations, whose payloads differ by a few bytes and fill
+//                 the same number of blocks, up to four waves per SIMD: 70,000
+//                 33 us (sorted 36), 220,000 61.5 us (65), 300,000 78 us (78).
 //   local         100,000 txs with 50,000 derived keys 73 us against 93 in
 //                 order; 1M txs 248 us against 257 globally binned, 256 blocks
 //                 of 7.66M txs 1,745 against 1,803.
@@ -475,7 +478,7 @@ Form form_of(const Plan &p, uint64_t waves, unsigned cus)
     if ((p.flags & ACE_ORDERED) || p.per_tx) return kInOrder;
     if (waves > kLocalMaxWaves) return p.mode == kBinned ? kGlobalBins : kLocal;
     if (p.flags & ACE_BUCKETED) return kLocal;
-    return waves <= 4ull * cus ? kInOrder : kLocal;
+    return waves <= (p.attest ? 16ull : 4ull) * cus ? kInOrder : kLocal;
 }
 
 // Shape of the local form: up to 64 wave tiles per CU one workgroup of 16
@@ -597,8 +600,8 @@ int enqueue_stages(const Plan &p, const Batch &bt, const ace_keyset *keys, const
         if ((graph || p.total_tx) && form == kInOrder) {
             unsigned g = (unsigned)waves;
             if (!pairs) {
-                g = grid_for(waves, per_tx ? kWavesPerWG : 1, 0x7fffffffu);
-                if (graph) g = std::min<unsigned>(g, tn.verify_wgs_per_cu * cus * (per_tx ? 1 : kWavesPerWG));
+                g = grid_for(waves, kWavesPerWG, 0x7fffffffu);
+                if (graph) g = std::min<unsigned>(g, tn.verify_wgs_per_cu * cus);
             }
             launch_ordered(p.attest, per_tx, pairs, g, s, bt, ks, hp, solo);
             if ((rc = launch_status("k_verify_ordered launch"))) return rc;

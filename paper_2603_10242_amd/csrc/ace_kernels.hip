@@ -526,11 +526,17 @@ __global__ void __launch_bounds__(kWG) ACE_WAVES(4) k_verify_ordered(Batch bt, K
         hkdf_prepare(hp, prep);
         __syncthreads();
     }
+    // A wave adds up its tiles' counts while they are in one block, and the
+    // workgroup's waves add theirs up at the end: atomics on one address take
+    // about 12 ns each, one after the other, and waves of equal messages end
+    // together (65,000 attestations 32 us with one per wave).
+    __shared__ uint32_t sum_block[kWavesPerWG], sum[kWavesPerWG];
     const Totals T = totals(bt);
     // grid-stride over wave tiles (wave-uniform loop bound)
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t wpw = blockDim.x >> 6;
-    for (uint64_t w = (uint64_t)blockIdx.x * wpw + wave; w < T.waves; w += (uint64_t)gridDim.x * wpw) {
+    uint32_t last = 0, acc = 0;
+    for (uint64_t w = (uint64_t)blockIdx.x * kWavesPerWG + wave; w < T.waves;
+         w += (uint64_t)gridDim.x * kWavesPerWG) {
         const uint32_t b = find_block<1>(bt, T, w);
         const DevBlock d = get_block(bt, T, b);
         const uint64_t i0 = 64ull * (w - d.wave0);
@@ -541,11 +547,30 @@ __global__ void __launch_bounds__(kWG) ACE_WAVES(4) k_verify_ordered(Batch bt, K
         if (active) live = load_tx<ATTEST>(d, i, ks, t);
         const bool valid = verify_lane<PER_TX_KEYS, ATTEST, !ATTEST, true>(live, t, &prep) && live;
         const unsigned long long m = __ballot(valid);
+        if (b != last) {
+            if (acc && lane_id() == 0) atomicAdd(get_block(bt, T, last).count, (unsigned long long)acc);
+            last = b;
+            acc = 0;
+        }
+        acc += (uint32_t)__popcll(m);
         if (lane_id() == 0) {
             d.bitmask[i0 >> 5] = (uint32_t)m;
             if (i0 + 32 < d.n) d.bitmask[(i0 >> 5) + 1] = (uint32_t)(m >> 32);
-            if (m) atomicAdd(d.count, (unsigned long long)__popcll(m));
         }
+    }
+    if (lane_id() == 0) {
+        sum_block[wave] = last;
+        sum[wave] = acc;
+    }
+    __syncthreads();
+    if (threadIdx.x < kWavesPerWG) {
+        // the first wave of each block's run of waves adds for all of them
+        const uint32_t b = sum_block[threadIdx.x];
+        uint32_t s = 0;
+        for (int v = 0; v < kWavesPerWG; ++v) s += sum_block[v] == b ? sum[v] : 0u;
+        bool first = true;
+        for (int v = 0; v < kWavesPerWG; ++v) first &= v >= (int)threadIdx.x || sum_block[v] != b;
+        if (first && s) atomicAdd(get_block(bt, T, b).count, (unsigned long long)s);
     }
 }
 

@@ -432,14 +432,6 @@ void launch_ordered(bool attest, bool per_tx, bool pairs, unsigned g, hipStream_
     }
 }
 
-template <bool AT>
-void launch_local_t(bool wide, unsigned g, hipStream_t s, const Batch &bt, const KeySource &ks,
-                    uint64_t wide_min)
-{
-    if (wide) hipLaunchKernelGGL((k_verify_local<AT, 16>), dim3(g), dim3(1024), 0, s, bt, ks, wide_min);
-    else hipLaunchKernelGGL((k_verify_local<AT, 8>), dim3(g), dim3(512), 0, s, bt, ks, wide_min);
-}
-
 // The derivation with the GPU to itself; `zero`: a count it clears, or NULL.
 int launch_derive(const uint8_t *rev, uint32_t n_id, uint8_t *key_out, uint32_t *mid_out, const HkdfParams &hp,
                   unsigned long long *zero, hipStream_t s)
@@ -484,14 +476,27 @@ Form form_of(const Plan &p, uint64_t waves, unsigned cus)
 // Shape of the local form: up to 64 wave tiles per CU one workgroup of 16
 // waves takes all of a CU's share, sorted together; beyond, two of 8 waves
 // run on a CU at a time, so that one's start and end are filled by the other.
+// `few`: so few that a SIMD holds one or two waves.
 struct LocalShape {
-    bool wide;
+    bool wide, few;
     uint32_t slots;
 };
 LocalShape local_shape(uint64_t waves, unsigned cus)
 {
     const bool wide = waves <= 64ull * cus;
-    return LocalShape{wide, wide ? cus : 2 * cus};
+    return LocalShape{wide, waves <= 8ull * cus, wide ? cus : 2 * cus};
+}
+
+template <bool AT>
+void launch_local_t(const LocalShape &sh, unsigned g, hipStream_t s, const Batch &bt, const KeySource &ks,
+                    uint64_t wide_min)
+{
+    if (!AT && sh.few)
+        hipLaunchKernelGGL((k_verify_local<false, 16, true>), dim3(g), dim3(1024), 0, s, bt, ks, wide_min);
+    else if (sh.wide)
+        hipLaunchKernelGGL((k_verify_local<AT, 16, false>), dim3(g), dim3(1024), 0, s, bt, ks, wide_min);
+    else
+        hipLaunchKernelGGL((k_verify_local<AT, 8, false>), dim3(g), dim3(512), 0, s, bt, ks, wide_min);
 }
 
 template <bool PT, bool PE, bool AT>
@@ -609,8 +614,8 @@ int enqueue_stages(const Plan &p, const Batch &bt, const ace_keyset *keys, const
             const LocalShape sh = local_shape(waves, cus);
             const unsigned g = local_share(waves, sh.slots).groups;
             const uint64_t wide_min = std::min<uint64_t>(tn.wide_min_len, kRecMaxLen);
-            if (p.attest) launch_local_t<true>(sh.wide, g, s, bt, ks, wide_min);
-            else launch_local_t<false>(sh.wide, g, s, bt, ks, wide_min);
+            if (p.attest) launch_local_t<true>(sh, g, s, bt, ks, wide_min);
+            else launch_local_t<false>(sh, g, s, bt, ks, wide_min);
             if ((rc = launch_status("k_verify_local launch"))) return rc;
         }
         prof_mark(prof, 3, s);

@@ -53,7 +53,7 @@ def sweep(n, n_id, n_blocks, seed):
 # wave tiles on a 256-CU device: one workgroup (up to 4), one wave per SIMD (1,024), one workgroup
 # per CU (16,384), two per CU and more
 @pytest.mark.parametrize("n,n_blocks", [(1, 1), (64, 1), (65, 1), (256, 1), (257, 1), (700, 9), (65_536, 1),
-                                        (65_537, 1), (66_000, 300), (131_071, 1), (1_048_576, 1),
+                                        (65_537, 1), (66_000, 300), (131_071, 1), (131_073, 1), (1_048_576, 1),
                                         (1_048_640, 1), (1_050_000, 41)])
 @pytest.mark.parametrize("form", ["hmac", "attest"])
 def test_open_calls_at_shape_edges(ace, n, n_blocks, form):

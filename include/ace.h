@@ -73,7 +73,8 @@ typedef enum {
 #define ACE_PERSISTENT 0x4u /* fixed grid of workgroups pulling wave tiles from a counter */
 #define ACE_PER_TX_KEYS 0x8u /* keyset of kind ACE_KEYS_REV: derive each transaction's key
                                 inside the verify kernel instead of once per identity */
-/* Neither ORDERED nor BUCKETED: the library picks (bucketed for large batches). */
+/* Neither ORDERED nor BUCKETED: the library picks (in order while a wave per SIMD
+   holds the call, grouped beyond). */
 
 /* Keyset kinds. */
 #define ACE_KEYS_MIDSTATE 0 /* d_mid[n_id][16]: cached HMAC midstates (from ace_derive_keys) */
@@ -215,9 +216,9 @@ ACE_API int ace_verify_attestations(const ace_keyset *keys, const ace_block *blo
  *     one GPU (on different streams, or from different threads, without
  *     ordering between them) race and give undefined results.  Calls ordered
  *     on one stream are safe; each clears what it needs.
- *   - With keys derived in a binned call, the derivation runs on `stream`
- *     before the binning passes (ace_verify_batch may run it beside them on
- *     a second stream).  Stage timing (ace_profile_enable) does not cover it.
+ *   - With keys derived in a globally binned call, the derivation runs on
+ *     `stream` before the binning passes (ace_verify_batch may run it beside
+ *     them on a second stream).  Stage timing (ace_profile_enable) does not cover it.
  */
 #define ACE_SCRATCH_BYTES (64u << 20)
 ACE_API int ace_verify_batch_noalloc(const ace_keyset *keys, const ace_block *blocks,
@@ -226,11 +227,15 @@ ACE_API int ace_verify_batch_noalloc(const ace_keyset *keys, const ace_block *bl
 /*
  * Tuning of the launch shapes (process-wide).  The autotuner measures the
  * candidates on the device and installs the fastest with ace_set_tuning.
- *   binned_min_tx      batches of at least this many transactions are binned
- *                      by block count when the caller leaves the mode open
+ *   binned_min_tx      batches of at least this many transactions are laid out
+ *                      as ACE_BUCKETED ones when the caller leaves the mode
+ *                      open (smaller ones may still be sorted by block count
+ *                      within workgroups, which needs no workspace)
  *   verify_wgs_per_cu  workgroups per CU of the persistent verify kernel and
  *                      of the graph's in-order verify ("tiles per CU")
- *   aux_wgs_per_cu     workgroups per CU of the binning and finalize passes
+ *   aux_wgs_per_cu     workgroups per CU of the global binning and finalize
+ *                      passes (batches of more than 2^17 wave tiles of 64
+ *                      transactions, and persistent ones)
  *   auto_persistent    1: binned batches in the open mode use the persistent
  *                      verify kernel
  *   derive_wgs_per_cu  workgroups per CU of the key derivation while it runs
@@ -273,10 +278,9 @@ ACE_API int ace_set_tuning(const ace_tuning *t);
  * fixed, into two graph instances that read their block list from pinned host
  * memory through a device-side plan kernel; so one capture replays for any
  * mix of block count, block sizes and message lengths within the maxima.
- * Every grid is fixed: the binned verify kernel is launched for the largest
- * batch (surplus waves exit at once) or, with ACE_PERSISTENT, as the
- * persistent kernel; the in-order form (flag ACE_ORDERED) is a grid-stride
- * kernel.  The launch tuning in force at ace_graph_create is captured with
+ * Every grid is fixed: the verify kernel is launched for the largest batch
+ * (surplus workgroups exit at once) or, with ACE_PERSISTENT, as the persistent
+ * kernel; the in-order form (flag ACE_ORDERED) is a grid-stride kernel.  The launch tuning in force at ace_graph_create is captured with
  * the graph; later ace_set_tuning calls do not change its replays.
  *   d_workspace  at least ace_graph_workspace_size() bytes, 256-byte aligned,
  *                owned by the graph until ace_graph_destroy.
@@ -380,9 +384,11 @@ ACE_API int ace_stream_create_host(ace_host_verify_fn fn, void *user, size_t are
  * kernel and the finalize pass.  ace_profile_read() waits for the recorded
  * events and returns the summed milliseconds of all profiled calls since the
  * last reset (reset != 0 clears them).  Stages a call did not run add 0.
- * In the binned form with keys derived in the call, the derivation runs on
- * a second stream beside the binning passes; the derive stage then reads
- * about 0 and bin_ms covers both, up to the join before the verify kernel.
+ * In the globally binned form with keys derived in the call, the derivation
+ * runs on a second stream beside the binning passes; the derive stage then
+ * reads about 0 and bin_ms covers both, up to the join before the verify
+ * kernel.  Calls sorted within workgroups have no binning stage, small calls
+ * derive each transaction's key in the verify kernel.
  */
 typedef struct {
     double derive_ms;
@@ -418,8 +424,8 @@ ACE_API size_t ace_merkle_workspace_size(const ace_merkle_tree *trees, uint32_t 
 
 /*
  * ace_merkle_roots -- the roots of n_trees trees in one pass: every leaf of
- * every tree hashed in parallel, then one launch per tree level over all
- * trees.  h-side `trees` is read before the call returns; d_workspace is at
+ * every tree hashed in parallel, then the levels, the narrow ones several to a
+ * launch.  h-side `trees` is read before the call returns; d_workspace is at
  * least ace_merkle_workspace_size() bytes, 256-byte aligned.  Total leaves
  * <= ACE_MAX_TX, n_trees < 2^24.
  */

@@ -13,7 +13,7 @@ namespace ace {
 // pads in one compression on neighbouring lanes) and the schedule of the padded
 // expand input (info || 0x01) with the round constants added, K[t] + W[t] for
 // all 64 rounds (FIPS 180-4 sec. 6.2.2 steps 1 and 3 with the message-dependent
-// part done once; the second wave, beside the first, where there is one).  The
+// part done once; the second wave, beside the first).  The
 // words come ready from the host.  Every workgroup's identities wait for this,
 // and in a small call nothing else runs: with the byte strings padded in the
 // kernel, both pads in turn on one wave and the schedule after them, a verify
@@ -22,7 +22,6 @@ template <class Params>
 __device__ __forceinline__ void hkdf_prepare(const Params &hp, HkdfPrep &out)
 {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool one_wave = blockDim.x <= 64;
     if (wave == 0) {
         uint32_t k0[16];
         if (hp.salt_blocks) {
@@ -54,7 +53,7 @@ __device__ __forceinline__ void hkdf_prepare(const Params &hp, HkdfPrep &out)
             for (int j = 0; j < 8; ++j) o[j] = s.h[j];
         }
     }
-    if (wave == 1 || (one_wave && wave == 0)) {
+    if (wave == 1) {
         // Expand input T(1) = HMAC(PRK, info || 0x01): after the 64-byte key
         // block the hashed stream is info || 0x01, bit length (64 + len + 1) * 8.
         // Lane q takes block q.

@@ -118,7 +118,7 @@ def test_graph_replays_of_changing_size(ace):
 
 
 @pytest.mark.parametrize("sizes", [[100_003], [7_000] * 36 + [0, 1], [3] * 139 + [1024], [5] * 140 + [1025],
-                                   [2] * 281, [262_145, 1, 2_000]])
+                                   [2] * 281, [262_145, 1, 2_000], [9] * 513, [513, 512, 511, 514, 1024]])
 def test_merkle_stages(ace, sizes):
     """Trees reduced by levels, by chunks of 1,024 nodes and by both, and tables
     of one, two and three launches."""

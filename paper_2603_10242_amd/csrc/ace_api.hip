@@ -544,13 +544,13 @@ int enqueue_stages(const Plan &p, const Batch &bt, const ace_keyset *keys, const
     ks.n_id = keys->n_id;
     ks.mid = nullptr;
     ks.rev = nullptr;
-    // Keys derived in the call.  In-order calls without a flag have at most one
-    // wave per SIMD: each lane derives its own transaction's key, which costs
-    // idle lanes and saves a launch and the midstates' way through memory.
+    // Keys derived in the call.  In an in-order call of at most one wave per SIMD
+    // each lane derives its own transaction's key, which costs idle lanes and
+    // saves a launch and the midstates' way through memory.
     // In the binned form the derivation (VALU-bound) runs on a second stream
     // beside the binning passes (memory-bound), which do not depend on it; the
     // verify kernel waits for both.
-    const bool per_tx = p.per_tx || (p.rev && form == kInOrder && !(p.flags & ACE_ORDERED));
+    const bool per_tx = p.per_tx || (p.rev && form == kInOrder && !(p.flags & ACE_ORDERED) && waves <= 4ull * cus);
     unsigned long long *const zero = graph || p.n_blocks > 1 ? nullptr : bt.one.count;  // else cleared already
     // in order with two waves per wave tile while each wave has its SIMD to itself
     const bool pairs = form == kInOrder && waves <= pair_verify_tiles();

@@ -1,21 +1,24 @@
 // ace_kernels.hip -- gfx950 kernels of the attestation check.
 //
-//   k_zero           clears the per-block counts and the binning control words.
-//   k_bin_count      histogram of transactions by inner block count.
-//   k_bin_scan       bin start positions, longest messages first.
-//   k_bin_scatter    transaction records into bin order.
-//   k_verify_*       Alg. 1 Phase 1a per transaction (in input order, sorted
-//                    by block count within a workgroup, or binned globally): inner hash of the message
+//   k_verify_*       Alg. 1 Phase 1a per transaction: inner hash of the message
 //                    from the cached ipad midstate, outer hash from the opad
 //                    midstate, constant-time compare with the credential,
 //                    wave64 ballot of the verdicts (also the paper's
 //                    attestation form, Def. 3.1 with Alg. 2's payload binding).
-//   k_finalize       bin-order verdicts back to input order.
+//                    By size: pair (two waves per 64 transactions), ordered,
+//                    local (sorted by block count in a workgroup), binned
+//                    (sorted over the whole call).
+//   k_bin_count      binned form: histogram of transactions by inner block count,
+//   k_bin_scan       bin start positions, longest messages first,
+//   k_bin_scatter    transaction records into bin order,
+//   k_finalize       bin-order verdicts back to input order,
 //   k_count          valid counts from the finished bitmasks.
+//   k_zero           clears counts and the binning control words.
+//   k_put_descs      block table of a call of several blocks.
 //   k_plan           device-side plan of a graph replay.
 // The key derivation (Def. 2.1) is in hkdf_kernels.hip, the two-wave forms for
-// small calls in pair_kernels.hip, the hash-chain
-// segments in chain_kernels.hip, the Merkle roots in merkle_kernels.hip.
+// small calls in pair_kernels.hip, the hash-chain segments in
+// chain_kernels.hip, the Merkle roots in merkle_kernels.hip.
 //
 // One transaction per lane.  Message bytes are read straight from HBM as
 // aligned dwords and turned into big-endian schedule words with one

@@ -457,16 +457,27 @@ int launch_derive(const uint8_t *rev, uint32_t n_id, uint8_t *key_out, uint32_t 
 //   local         100,000 txs with 50,000 derived keys 73 us against 93 in
 //                 order; 1M txs 248 us against 257 globally binned, 256 blocks
 //                 of 7.66M txs 1,745 against 1,803.
+//                 Lengths are not known on the host: where all are equal and
+//                 a SIMD holds two to four waves, the sort is lost time
+//                 (128-byte messages, 130,000 txs 35.5 us against 32.5 in order,
+//                 ragged ones 76 against 132).
 //   global bins   beyond kLocalMaxWaves wave tiles its fuller waves make up for
 //                 its passes: 16M txs with 1M derived keys 4,000-4,130 us
-//                 against 4,105-4,180 locally sorted.  Persistent waves and
+//                 against 4,105-4,180 locally sorted.  From 64 wave tiles per
+//                 CU too when keys are derived in the call: the passes hide
+//                 under the derivation on the second stream, 2.5M txs with
+//                 625k identities 760 us against 787 locally sorted, 4M with 1M
+//                 1,185 against 1,220 (below, 1M with 250k: 346 locally sorted,
+//                 349 binned).  Attestations, all of one block count, gain
+//                 more from the local form's single pass.  Persistent waves and
 //                 per-transaction keys, on request, exist in this form only.
 enum Form { kInOrder, kLocal, kGlobalBins };
 constexpr uint64_t kLocalMaxWaves = 1u << 17;
 
-Form form_of(const Plan &p, uint64_t waves, unsigned cus)
+Form form_of(const Plan &p, uint64_t waves, unsigned cus, bool fork)
 {
     if (p.mode == kBinned && (p.persistent || p.per_tx)) return kGlobalBins;
+    if (p.mode == kBinned && p.rev && fork && !p.attest && waves > 64ull * cus) return kGlobalBins;
     if ((p.flags & ACE_ORDERED) || p.per_tx) return kInOrder;
     if (waves > kLocalMaxWaves) return p.mode == kBinned ? kGlobalBins : kLocal;
     if (p.flags & ACE_BUCKETED) return kLocal;
@@ -537,7 +548,7 @@ int enqueue_stages(const Plan &p, const Batch &bt, const ace_keyset *keys, const
     Ctrl *ctrl = reinterpret_cast<Ctrl *>(ws + p.off_ctrl);
     // wave tiles: the call's, or the most a replay can have
     const uint64_t waves = graph ? (p.total_tx + 63) / 64 + p.n_blocks : p.total_waves;
-    const Form form = form_of(p, waves, cus);
+    const Form form = form_of(p, waves, cus, fork);
     const bool binned = form == kGlobalBins;
 
     KeySource ks;

@@ -81,6 +81,7 @@ __device__ __forceinline__ Totals totals(const Batch &bt)
         t.share.groups = uniform32(bt.hdr->share.groups);
         t.share.base = uniform32(bt.hdr->share.base);
         t.share.extra = uniform32(bt.hdr->share.extra);
+        t.share.slots = uniform32(bt.hdr->share.slots);
         t.inline_one = false;
     } else {
         t.n_blocks = bt.n_blocks;
@@ -704,8 +705,8 @@ __global__ void __launch_bounds__(128) k_verify_pair(Batch bt, KeySource ks, Hkd
 }
 
 // ------------------------------------------------------------------------------------------
-// k_verify, local form: a workgroup takes a run of wave tiles (64 transactions
-// of one block each, in input order, over all blocks of the call), sorts their
+// k_verify, local form: a workgroup takes a share of the wave tiles (64
+// transactions of one block each; see LocalTiles for which), sorts their
 // transactions by block count in LDS, longest first, and its waves take 64 of
 // them at a time, so that a wave's lanes finish together; verdict bits return
 // to input order in LDS, from where they go to the bitmasks and counts.
@@ -773,8 +774,8 @@ __global__ void __launch_bounds__(64 * NW) ACE_WAVES(4) k_verify_local(Batch bt,
     // instead of 12)
     __builtin_amdgcn_s_setprio(3);
     if (blockIdx.x >= sh.groups) return;  // the whole workgroup
-    const uint32_t U = sh.base + (blockIdx.x < sh.extra ? 1u : 0u);  // <= kLocalUnits
-    const uint32_t u0 = blockIdx.x * sh.base + (blockIdx.x < sh.extra ? blockIdx.x : sh.extra);
+    const LocalTiles mine = local_tiles(sh, blockIdx.x);
+    const uint32_t U = mine.count;  // <= kLocalUnits
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = lane_id();
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -782,7 +783,7 @@ __global__ void __launch_bounds__(64 * NW) ACE_WAVES(4) k_verify_local(Batch bt,
     if (tid < kBins) hist[tid] = 0;
     if (tid == 0) next_tile = NW;
     if (tid < U) {
-        const uint32_t w = u0 + tid;
+        const uint32_t w = local_tile(mine, tid);
         const uint32_t b = find_block<1>(bt, T, w);
         const DevBlock d = get_block(bt, T, b);
         const uint64_t i0 = 64ull * (w - d.wave0);
@@ -894,7 +895,7 @@ __global__ void __launch_bounds__(64 * NW) ACE_WAVES(4) k_verify_local(Batch bt,
     __syncthreads();
     static_assert(kLocalUnits <= 64, "one wave writes the results");
     if (wave == 0) {
-        // lane u: tile u's bitmask words, then its count, added up per block
+        // lane u: tile u's bitmask words, then its count, one atomic per block
         uint32_t b = 0, c = 0;
         if (lane < U) {
             const Unit &x = unit[lane];
@@ -905,15 +906,21 @@ __global__ void __launch_bounds__(64 * NW) ACE_WAVES(4) k_verify_local(Batch bt,
             if (x.n > 32) out[1] = hi;
             c = __popc(lo) + __popc(hi);
         }
-        for (uint32_t at = 0; at < U;) {  // a block's tiles are consecutive lanes
-            const uint32_t b0 = __shfl(b, at);
-            const bool mine = lane < U && b == b0;
-            uint32_t s = mine ? c : 0u;
+        // tiles ascend with the lane, so a block's are consecutive lanes: the
+        // last of them adds their sum
+        uint32_t s = c;  // counts up to this lane
 #pragma unroll
-            for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d);
-            if (lane == at && s) atomicAdd(get_block(bt, T, b0).count, (unsigned long long)s);
-            at += __popcll(__ballot(mine));
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t v = __shfl_up(s, d);
+            if ((int)lane >= d) s += v;
         }
+        const uint32_t below = __shfl_up(b, 1), above = __shfl_down(b, 1);
+        const unsigned long long heads = __ballot(lane == 0 || b != below);
+        const int head = 63 - __clzll((long long)(heads & (~0ull >> (63 - lane))));
+        const uint32_t before = __shfl(s, head ? head - 1 : 0);
+        const uint32_t sum = head ? s - before : s;
+        if (lane < U && (lane + 1 == U || b != above) && sum)
+            atomicAdd(get_block(bt, T, b).count, (unsigned long long)sum);
     }
 }
 

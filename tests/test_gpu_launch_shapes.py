@@ -117,6 +117,87 @@ def test_graph_replays_of_changing_size(ace):
     g.close()
 
 
+def all_valid(ace, n, bad=()):
+    """n copies of one valid transaction (64-byte message), those at `bad` with a
+    flipped credential bit: block, keyset, expected mask."""
+    import torch
+    w = W.generate("copies", 11, n=64, n_id=1, lengths=lambda r, k: np.full(k, 64), p_invalid=0.0)
+    ks = ace.midstate_keyset(ace.to_device(w.rev), w.salt, w.info)
+    tags = torch.from_numpy(w.tags[:1].copy()).cuda().repeat(n, 1)
+    truth = np.ones(n, bool)
+    for i in bad:
+        tags[i, 5] ^= 1
+        truth[i] = False
+    blk = ace.DeviceBlock(ace.to_device(w.msg[:64]).repeat(n), torch.arange(n + 1, device="cuda") * 64,
+                          torch.zeros(n, dtype=torch.int32, device="cuda"), tags,
+                          torch.full(((n + 31) // 32,), -1, dtype=torch.int32, device="cuda"),
+                          torch.full((1,), 99, dtype=torch.int64, device="cuda"), n)
+    return blk, ks, truth
+
+
+# wave tiles: none to a few per workgroup, the edges of a dealt row, of one and two rounds of
+# workgroups, of both workgroup widths
+@pytest.mark.parametrize("tiles", [1, 2, 255, 256, 257, 511, 513, 767, 1_024, 1_025, 1_281, 2_047, 2_048, 2_049, 2_304,
+                                   2_305, 4_999, 16_383, 16_384, 16_385, 32_767, 32_769, 40_001, 65_537])
+def test_every_tile_once_in_the_local_form(ace, tiles):
+    """Whichever workgroup takes which tiles: every mask word written, every
+    transaction counted once."""
+    import torch
+    n = 64 * tiles - 29
+    blk, ks, truth = all_valid(ace, n, bad={0, n // 3, n - 1})
+    print("tiles=%d" % tiles, flush=True)
+    ace.verify_batch(ks, [blk], flags=ace.ACE_BUCKETED)
+    torch.cuda.synchronize()
+    mask, count = blk.result()
+    assert count == int(truth.sum())
+    assert np.array_equal(mask, W.pack_bits(truth))
+
+
+def lengths_in_order(order, n):
+    r = np.random.default_rng(n)
+    L = W.lognormal_lengths(r, n)
+    if order == "one place":
+        L = r.integers(64, 100, n)
+        L[n // 2: n // 2 + n // 128] = 1_200
+    elif order == "runs of 128 tiles":
+        L = np.where(np.arange(n) // 8_192 % 2, 80, 800)
+    return L.astype(np.int64)
+
+
+@pytest.mark.parametrize("n", [300_000, 1_000_000])
+@pytest.mark.parametrize("order", ["sorted", "one place", "runs of 128 tiles"])
+def test_time_of_ordered_lengths(ace, n, order):
+    """A call whose message lengths are ordered takes about the time of the same
+    messages shuffled: at most 1.5 times (with one consecutive share per
+    workgroup 1.5 to 5 times)."""
+    import torch
+    L = lengths_in_order(order, n)
+    ks = ace.midstate_keyset(torch.zeros((64, 32), dtype=torch.uint8, device="cuda"), b"s", b"i")
+    us = {}
+    for how in ("ordered", "shuffled"):
+        K = np.random.default_rng(1).permutation(L) if how == "shuffled" else np.sort(L) if order == "sorted" else L
+        off = np.zeros(n + 1, np.int64)
+        np.cumsum(K, out=off[1:])
+        blk = ace.DeviceBlock(torch.zeros(int(off[-1]), dtype=torch.uint8, device="cuda"), torch.from_numpy(off).cuda(),
+                              torch.arange(n, dtype=torch.int32, device="cuda") % 64,
+                              torch.zeros((n, 32), dtype=torch.uint8, device="cuda"),
+                              torch.zeros((n + 31) // 32, dtype=torch.int32, device="cuda"),
+                              torch.zeros(1, dtype=torch.int64, device="cuda"), n)
+        ws = ace.workspace(ace.verify_workspace_size(ks, [blk]))
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                ace.verify_batch(ks, [blk], ws=ws)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 100)
+        us[how] = best
+    print("n=%d %s: %.1f us, shuffled %.1f us" % (n, order, us["ordered"], us["shuffled"]), flush=True)
+    assert us["ordered"] <= 1.5 * us["shuffled"]
+
+
 @pytest.mark.parametrize("sizes", [[100_003], [7_000] * 36 + [0, 1], [3] * 139 + [1024], [5] * 140 + [1025],
                                    [2] * 281, [262_145, 1, 2_000], [9] * 513, [513, 512, 511, 514, 1024]])
 def test_merkle_stages(ace, sizes):

@@ -455,16 +455,19 @@ int launch_derive(const uint8_t *rev, uint32_t n_id, uint8_t *key_out, uint32_t 
 //                 the same number of blocks, up to four waves per SIMD: 70,000
 //                 33 us (sorted 36), 220,000 61.5 us (65), 300,000 78 us (78).
 //   local         100,000 txs with 50,000 derived keys 73 us against 93 in
-//                 order; 1M txs 248 us against 257 globally binned, 256 blocks
-//                 of 7.66M txs 1,745 against 1,803.
+//                 order; 1M txs 248 us against 257 globally binned, 2M
+//                 attestations 490 against 512.
 //                 Lengths are not known on the host: where all are equal and
 //                 a SIMD holds two to four waves, the sort is lost time
 //                 (128-byte messages, 130,000 txs 35.5 us against 32.5 in order,
 //                 ragged ones 76 against 132).
-//   global bins   beyond kLocalMaxWaves wave tiles its fuller waves make up for
-//                 its passes: 16M txs with 1M derived keys 4,000-4,130 us
-//                 against 4,105-4,180 locally sorted.  From 64 wave tiles per
-//                 CU too when keys are derived in the call: the passes hide
+//   global bins   beyond one round of the local form's workgroups (2M txs 467-470
+//                 us either way, 4M 906-920).  In a later round the longest
+//                 messages start late, and each round waits for its own: 7M txs of
+//                 64 to 20,000 bytes (Pareto) 4,540 us in four rounds against
+//                 1,700, a tenth of 1,200 bytes among 100 1,475 against 1,335;
+//                 lognormal lengths gained 2%.  From 64 wave tiles per CU too
+//                 when keys are derived in the call: the passes hide
 //                 under the derivation on the second stream, 2.5M txs with
 //                 625k identities 760 us against 787 locally sorted, 4M with 1M
 //                 1,185 against 1,220 (below, 1M with 250k: 346 locally sorted,
@@ -472,14 +475,12 @@ int launch_derive(const uint8_t *rev, uint32_t n_id, uint8_t *key_out, uint32_t 
 //                 more from the local form's single pass.  Persistent waves and
 //                 per-transaction keys, on request, exist in this form only.
 enum Form { kInOrder, kLocal, kGlobalBins };
-constexpr uint64_t kLocalMaxWaves = 1u << 17;
-
 Form form_of(const Plan &p, uint64_t waves, unsigned cus, bool fork)
 {
     if (p.mode == kBinned && (p.persistent || p.per_tx)) return kGlobalBins;
     if (p.mode == kBinned && p.rev && fork && !p.attest && waves > 64ull * cus) return kGlobalBins;
     if ((p.flags & ACE_ORDERED) || p.per_tx) return kInOrder;
-    if (waves > kLocalMaxWaves) return p.mode == kBinned ? kGlobalBins : kLocal;
+    if (waves > 2ull * cus * kLocalUnits) return p.mode == kBinned ? kGlobalBins : kLocal;
     if (p.flags & ACE_BUCKETED) return kLocal;
     return waves <= (p.attest ? 16ull : 4ull) * cus ? kInOrder : kLocal;
 }

@@ -762,6 +762,7 @@ __global__ void __launch_bounds__(64 * NW) ACE_WAVES(4) k_verify_local(Batch bt,
         uint32_t x;    // 64 * tile + transaction
     };
     constexpr int kPerThread = kLocalUnits / NW;
+    constexpr bool kEven = NW == 16;  // the shape of calls with few tiles per workgroup
     __shared__ Unit unit[kLocalUnits];
     __shared__ Rec rec[64 * kLocalUnits];
     __shared__ uint32_t mask[2 * kLocalUnits];
@@ -822,29 +823,42 @@ __global__ void __launch_bounds__(64 * NW) ACE_WAVES(4) k_verify_local(Batch bt,
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) {
         bin[k] = kBins;
-        if (a[k] <= e[k] && who[k] < ks.n_id) {
-            bin[k] = bin_of_length(e[k] - a[k]);
+        if (a[k] <= e[k] && who[k] < ks.n_id) bin[k] = bin_of_length(e[k] - a[k]);
+        const uint32_t b0 = uniform32(bin[k]);
+        if (kEven && __ballot(bin[k] != b0) == 0) {
+            // one bin for the whole wave: one atomic (64 on one address take turns)
+            if (b0 < kBins) rank[k] = atomicAdd(&hist[b0], 1u);
+        } else if (bin[k] < kBins) {
             rank[k] = atomicAdd(&hist[bin[k]], 1u);
         }
     }
     __syncthreads();
-    if (wave == 0) {
-        // start of every bin, longest first (lane l: bin 63 - l)
-        const uint32_t c = hist[kBins - 1 - lane];
-        uint32_t s = c;
+    // Messages all of one block count need no sorting, and with no more than a
+    // tile per wave every wave keeps the one it has loaded (128-byte messages,
+    // 250,000 transactions 52.5 -> 49.5 us, 100,000 30.7 -> 28.8; in order, whose
+    // waves need no prologue at all, 50.0 and 30.3).  Lanes without a transaction
+    // then have a record that says so.
+    const unsigned long long bins = __ballot(hist[lane] != 0);
+    const bool even = kEven && U <= NW && __popcll(bins) == 1;
+    if (!even) {
+        if (wave == 0) {
+            // start of every bin, longest first (lane l: bin 63 - l)
+            const uint32_t c = hist[kBins - 1 - lane];
+            uint32_t s = c;
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t v = __shfl_up(s, d);
-            if ((int)lane >= d) s += v;
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t v = __shfl_up(s, d);
+                if ((int)lane >= d) s += v;
+            }
+            start[kBins - 1 - lane] = s - c;
+            if (lane == 63) n_live = s;
         }
-        start[kBins - 1 - lane] = s - c;
-        if (lane == 63) n_live = s;
+        __syncthreads();
     }
-    __syncthreads();
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) {
+        const uint32_t u = wave + k * NW;
         if (bin[k] < kBins) {
-            const uint32_t u = wave + k * NW;
             const uint64_t rel = a[k] - unit[u].off0, L = e[k] - a[k];
             Rec r;
             r.rel = (uint32_t)rel;
@@ -852,23 +866,28 @@ __global__ void __launch_bounds__(64 * NW) ACE_WAVES(4) k_verify_local(Batch bt,
                                                : (uint32_t)L | (e[k] + kOverread <= unit[u].area_end ? 0u : kRecNearEnd);
             r.id = who[k];
             r.x = 64u * u + lane;
-            rec[start[bin[k]] + rank[k]] = r;
+            rec[even ? r.x : start[bin[k]] + rank[k]] = r;
+        } else if (even) {
+            rec[64u * u + lane].id = kRecInvalid;
         }
     }
-    __syncthreads();
+    if (!even) __syncthreads();
 
     // Tiles of 64 in sorted order.  The first NW go to the waves so that each
     // SIMD's share is even when there are few (waves w and w + 4 share a SIMD:
     // every second row of four in reverse); the others are taken one by one.
-    const uint32_t live_n = n_live;
+    const uint32_t live_n = even ? 64 * U : n_live;
     set_row_priority(wave >> 2);
     const uint32_t tiles = (live_n + 63) >> 6;
-    uint32_t tile = (wave & 4u) ? (wave & ~3u) + 3u - (wave & 3u) : wave;
+    uint32_t tile = (wave & 4u) && !even ? (wave & ~3u) + 3u - (wave & 3u) : wave;
     while (tile < tiles) {
-        // the last tiles at equal priority: the low rows would be left with theirs
-        if (tile + 2 * NW >= tiles) __builtin_amdgcn_s_setprio(0);
+        // The last tiles at equal priority: the low rows would be left with
+        // theirs.  A single pass keeps its rows' (500,000 transactions of 1,000
+        // bytes 387 -> 342 us), except with one or two waves per SIMD (66,000-130,000
+        // of lognormal lengths 75 us, 78 with rows).
+        if ((AHEAD || tiles > NW) && tile + 2 * NW >= tiles) __builtin_amdgcn_s_setprio(0);
         const uint32_t p = 64 * tile + lane;
-        const bool live = p < live_n;
+        const bool live = p < live_n && (!kEven || rec[p].id != kRecInvalid);
         uint32_t x = 0;
         TxRef t{};
         if (live) {
@@ -891,7 +910,8 @@ __global__ void __launch_bounds__(64 * NW) ACE_WAVES(4) k_verify_local(Batch bt,
         if (verify_lane<false, ATTEST, true, AHEAD, ATTEST>(live, t, nullptr)) atomicOr(&mask[x >> 5], 1u << (x & 31u));
         // every lane takes part in the atomic, so that no divergent branch
         // precedes the readfirstlane
-        tile = __builtin_amdgcn_readfirstlane(atomicAdd(&next_tile, lane == 0 ? 1u : 0u));
+        if (even) tile += NW;
+        else tile = __builtin_amdgcn_readfirstlane(atomicAdd(&next_tile, lane == 0 ? 1u : 0u));
     }
     __syncthreads();
     static_assert(kLocalUnits <= 64, "one wave writes the results");

@@ -220,6 +220,38 @@ def test_time_of_a_few_long_messages(ace, n):
     assert mixed <= 1.2 * short + 1.5 * chain
 
 
+# wave tiles per workgroup on a 256-CU device: one, a few, sixteen (the most that are not sorted
+# where all are of one block count) and seventeen
+@pytest.mark.parametrize("n", [50, 20_000, 65_600, 100_001, 262_144, 262_145])
+@pytest.mark.parametrize("form", ["hmac", "attest"])
+def test_messages_of_one_block_count(ace, n, form):
+    """Lengths that all fill the same number of blocks, some transactions invalid,
+    some identities unregistered, then (last) every identity unregistered."""
+    import torch
+    n_id = max(2, min(n // 4, 5_000))
+    even = lambda r, k: r.integers(120, 170, k)  # three blocks after the key block, or without it
+    if form == "attest":
+        w = W.paper_attestations(n=n, n_id=n_id, seed=n, lengths=even)
+        msg, off, tags, salt = w.payload, w.poff, w.att, w.domain
+    else:
+        w = W.generate("even", n, n=n, n_id=n_id, lengths=even, p_invalid=0.02)
+        msg, off, tags, salt = w.msg, w.off, w.tags, w.salt
+    print("%s n=%d" % (form, n), flush=True)
+    check = oracle.verify_attest if form == "attest" else oracle.verify_batch
+    ks = ace.midstate_keyset(ace.to_device(w.rev), salt, w.info)
+    ids = w.ids.copy()
+    for gone in (slice(0, 0), slice(3, None, 1_009), slice(n // 2, n // 2 + 100), slice(None)):
+        ids[gone] = n_id + 1
+        blk = ace.upload_block(msg, off, ids, tags, record_bytes=72 if form == "attest" else 32)
+        blk.bitmask.fill_(-1)
+        blk.count.fill_(99)
+        (ace.verify_attestations if form == "attest" else ace.verify_batch)(ks, [blk], flags=ace.ACE_BUCKETED)
+        torch.cuda.synchronize()
+        mask, count = blk.result()
+        omask, ocount = check(w.keys, msg, off, ids, tags, 8)
+        assert count == ocount and np.array_equal(mask, omask)
+
+
 @pytest.mark.parametrize("sizes", [[100_003], [7_000] * 36 + [0, 1], [3] * 139 + [1024], [5] * 140 + [1025],
                                    [2] * 281, [262_145, 1, 2_000], [9] * 513, [513, 512, 511, 514, 1024]])
 def test_merkle_stages(ace, sizes):

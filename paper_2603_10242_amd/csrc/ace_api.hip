@@ -450,17 +450,15 @@ int launch_derive(const uint8_t *rev, uint32_t n_id, uint8_t *key_out, uint32_t 
 // The verify form of a call (or, with the maxima's wave tiles, of a graph).
 //   in order      at most one wave per SIMD: the longest message's chain takes
 //                 the whole time, and sorting could not shorten it (65,000
-//                 transactions 75 us, 70,000 locally sorted 82, in order 170).
-//                 Attestations, whose payloads differ by a few bytes and fill
-//                 the same number of blocks, up to four waves per SIMD: 70,000
-//                 33 us (sorted 36), 220,000 61.5 us (65), 300,000 78 us (78).
+//                 transactions 75 us, 70,000 locally sorted 75, in order 170).
 //   local         100,000 txs with 50,000 derived keys 73 us against 93 in
 //                 order; 1M txs 248 us against 257 globally binned, 2M
 //                 attestations 490 against 512.
-//                 Lengths are not known on the host: where all are equal and
-//                 a SIMD holds two to four waves, the sort is lost time
-//                 (128-byte messages, 130,000 txs 35.5 us against 32.5 in order,
-//                 ragged ones 76 against 132).
+//                 Lengths are not known on the host, but where all fill the same
+//                 number of blocks no time is lost (250,000 txs of 128 bytes
+//                 49.5 us, 50.0 in order; attestations with payloads of 130-154
+//                 bytes, 70,000 32.5 against 31, 260,000 57.4 against 58, of up
+//                 to 1,200 bytes 75 against 132 and 138 against 220).
 //   global bins   beyond one round of the local form's workgroups (2M txs 467-470
 //                 us either way, 4M 906-920).  In a later round the longest
 //                 messages start late, and each round waits for its own: 7M txs of
@@ -482,7 +480,7 @@ Form form_of(const Plan &p, uint64_t waves, unsigned cus, bool fork)
     if ((p.flags & ACE_ORDERED) || p.per_tx) return kInOrder;
     if (waves > 2ull * cus * kLocalUnits) return p.mode == kBinned ? kGlobalBins : kLocal;
     if (p.flags & ACE_BUCKETED) return kLocal;
-    return waves <= (p.attest ? 16ull : 4ull) * cus ? kInOrder : kLocal;
+    return waves <= 4ull * cus ? kInOrder : kLocal;
 }
 
 // Shape of the local form: up to 64 wave tiles per CU one workgroup of 16
@@ -556,13 +554,13 @@ int enqueue_stages(const Plan &p, const Batch &bt, const ace_keyset *keys, const
     ks.n_id = keys->n_id;
     ks.mid = nullptr;
     ks.rev = nullptr;
-    // Keys derived in the call.  In an in-order call of at most one wave per SIMD
-    // each lane derives its own transaction's key, which costs idle lanes and
+    // Keys derived in the call.  In an in-order call (at most one wave per SIMD,
+    // unless it asks for that form) each lane derives its own transaction's key, which costs idle lanes and
     // saves a launch and the midstates' way through memory.
     // In the binned form the derivation (VALU-bound) runs on a second stream
     // beside the binning passes (memory-bound), which do not depend on it; the
     // verify kernel waits for both.
-    const bool per_tx = p.per_tx || (p.rev && form == kInOrder && !(p.flags & ACE_ORDERED) && waves <= 4ull * cus);
+    const bool per_tx = p.per_tx || (p.rev && form == kInOrder && !(p.flags & ACE_ORDERED));
     unsigned long long *const zero = graph || p.n_blocks > 1 ? nullptr : bt.one.count;  // else cleared already
     // in order with two waves per wave tile while each wave has its SIMD to itself
     const bool pairs = form == kInOrder && waves <= pair_verify_tiles();

@@ -153,26 +153,27 @@ def test_every_tile_once_in_the_local_form(ace, tiles):
     assert np.array_equal(mask, W.pack_bits(truth))
 
 
-def time_of_lengths(ace, L, reps=10):
-    """Microseconds of an open call over messages of these lengths (a tensor on
-    the device), resident keys; the best of five."""
+def time_of_lengths(ace, L, reps=10, attest=False, flags=0):
+    """Microseconds of a call over messages of these lengths (a tensor on the
+    device), resident keys; the best of five."""
     import torch
     n = L.numel()
+    verify = ace.verify_attestations if attest else ace.verify_batch
     ks = ace.midstate_keyset(torch.zeros((64, 32), dtype=torch.uint8, device="cuda"), b"s", b"i")
     off = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
     torch.cumsum(L, 0, out=off[1:])
     blk = ace.DeviceBlock(torch.zeros(int(off[-1]), dtype=torch.uint8, device="cuda"), off,
                           torch.arange(n, dtype=torch.int32, device="cuda") % 64,
-                          torch.zeros((n, 32), dtype=torch.uint8, device="cuda"),
+                          torch.zeros((n, 72 if attest else 32), dtype=torch.uint8, device="cuda"),
                           torch.zeros((n + 31) // 32, dtype=torch.int32, device="cuda"),
                           torch.zeros(1, dtype=torch.int64, device="cuda"), n)
-    ws = ace.workspace(ace.verify_workspace_size(ks, [blk]))
+    ws = ace.workspace(ace.verify_workspace_size(ks, [blk], flags))
     best = float("inf")
     for _ in range(5):
         a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         a.record()
         for _ in range(reps):
-            ace.verify_batch(ks, [blk], ws=ws)
+            verify(ks, [blk], ws=ws, flags=flags)
         b.record()
         torch.cuda.synchronize()
         best = min(best, a.elapsed_time(b) * 1e3 / reps)
@@ -218,6 +219,20 @@ def test_time_of_a_few_long_messages(ace, n):
     print("n=%d: %.0f us, all short %.0f, one long message alone %.0f" % (n, mixed, short, chain), flush=True)
     # the long messages' own blocks are a tenth of the others'
     assert mixed <= 1.2 * short + 1.5 * chain
+
+
+@pytest.mark.parametrize("n", [100_000, 200_000])
+@pytest.mark.parametrize("lengths", ["130-154", "0-1200"])
+def test_time_of_open_attestations(ace, n, lengths):
+    """An open call of attestations takes the form that suits its payloads: at most
+    1.25 times the faster of in order and sorted (in order, payloads of 0 to 1,200
+    bytes took 1.5 times)."""
+    import torch
+    lo, hi = (130, 155) if lengths == "130-154" else (0, 1_201)
+    L = torch.randint(lo, hi, (n,), device="cuda")
+    us = [time_of_lengths(ace, L, attest=True, flags=f) for f in (0, ace.ACE_ORDERED, ace.ACE_BUCKETED)]
+    print("n=%d %s: open %.1f us, in order %.1f, sorted %.1f" % (n, lengths, *us), flush=True)
+    assert us[0] <= 1.25 * min(us[1:])
 
 
 # wave tiles per workgroup on a 256-CU device: one, a few, sixteen (the most that are not sorted

@@ -55,10 +55,12 @@ inline bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_
 constexpr unsigned kDeriveWgsPerCu = 4;
 
 // ace_derive_keys_multi: from this many tiles of 256 keys per CU over all its
-// parameter sets on, a workgroup derives two tiles (one preparation for both;
-// 9 streams of 131,072 identities 322 us against 347 with one preparation per
-// tile).  Fewer tiles keep one each: every CU has its five resident workgroups
-// only up to two rounds of them.
+// parameter sets on, a workgroup derives two tiles (one preparation for both)
+// where the CUs' shares come out even: 4,608 tiles (9 streams of 131,072
+// identities) 320 us against 324 with one each, 5,000 353 against 359.  One
+// tile over an even share costs every workgroup's second tile: 2,600 tiles 217 us
+// against 201, 3,600 284 against 270.  Below, every CU has its resident
+// workgroups in up to two rounds of one tile each.
 constexpr uint64_t kMultiStrideMin = 10;
 
 // Compute units of the current device (cached per device).
@@ -831,7 +833,8 @@ ACE_API int ace_derive_keys_multi(const uint8_t *d_rev, uint32_t n_id,
             if (int rc = launch_status("k_derive_pair launch")) return rc;
             continue;
         }
-        const uint64_t per = tiles * mp.count >= kMultiStrideMin * (uint64_t)cu_count() ? 2 : 1;
+        const uint64_t all = tiles * mp.count, cus = (uint64_t)cu_count();
+        const uint64_t per = all >= kMultiStrideMin * cus && (all + cus - 1) / cus % 2 == 0 ? 2 : 1;
         const unsigned gx = (unsigned)((tiles + per - 1) / per);
         hipLaunchKernelGGL(k_derive_multi, dim3(gx, mp.count), dim3(kWG), 0, s, d_rev, n_id, d_key_out,
                            d_mid_out, mp);

@@ -39,6 +39,35 @@ def test_derive_multi_tiles_per_workgroup(ace, n_id, n_streams):
         assert np.array_equal(got[k], np.asarray(want).reshape(-1, 16)), k
 
 
+@pytest.mark.parametrize("n_id,n_streams", [(80_123, 9), (72_706, 9)])
+def test_derive_multi_odd_tiles(ace, n_id, n_streams):
+    """313 and 285 tiles per stream: an odd number with two tiles per workgroup
+    (2,817 tiles, an even share of the CUs) and with one (2,565)."""
+    test_derive_multi_tiles_per_workgroup(ace, n_id, n_streams)
+
+
+def test_time_of_derivations_past_an_even_share(ace):
+    """40 tiles more than ten per CU cost about one round of one tile, at most 14%
+    (two tiles per workgroup: a round of two, 18%)."""
+    import torch
+    us = []
+    for tiles in (2_560, 2_600):
+        rev = torch.zeros((256 * tiles, 32), dtype=torch.uint8, device="cuda")
+        mid = torch.empty((256 * tiles, 16), dtype=torch.int32, device="cuda")
+        best = float("inf")
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                ace.derive_keys_multi(rev, [(b"s", b"i")], mid_out=mid)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 100)
+        us.append(best)
+    print("2,560 tiles %.1f us, 2,600 %.1f" % tuple(us), flush=True)
+    assert us[1] <= 1.14 * us[0]
+
+
 def attestations(n, n_id, n_blocks, seed):
     w = W.paper_attestations(n=n, n_id=n_id, seed=seed, lengths=lambda r, k: r.integers(0, 400, size=k))
     return w, w.payload, w.poff, w.att, w.domain

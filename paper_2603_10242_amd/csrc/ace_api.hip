@@ -1013,9 +1013,15 @@ ACE_API int ace_merkle_roots(const ace_merkle_tree *trees, uint32_t n_trees, voi
             if ((rc = launch_status("k_merkle_chunk launch"))) return rc;
         }
     }
-    hipLaunchKernelGGL(k_merkle_chunk, dim3(n_trees), dim3(kTopWG), 0, s, table, n_trees,
-                       (const unsigned long long *)nullptr, k, 1u, nodes);
-    return launch_status("k_merkle_chunk launch");
+    // a workgroup per tree; a launch has fewer than 2^32 threads
+    constexpr uint32_t kMaxTrees = 1u << 22;
+    for (uint32_t b = 0; b < n_trees; b += kMaxTrees) {
+        const uint32_t m = std::min(kMaxTrees, n_trees - b);
+        hipLaunchKernelGGL(k_merkle_chunk, dim3(m), dim3(kTopWG), 0, s, table + b, m,
+                           (const unsigned long long *)nullptr, k, 1u, nodes);
+        if ((rc = launch_status("k_merkle_chunk launch"))) return rc;
+    }
+    return ACE_OK;
 }
 
 ACE_API size_t ace_verify_workspace_size(const ace_keyset *keys, const ace_block *blocks,

@@ -125,3 +125,30 @@ def test_decreasing_offsets_hash_as_empty(ace):
     data = np.arange(40, dtype=np.uint8)
     off = np.array([0, 10, 4, 30, 40], np.uint64)
     assert np.array_equal(gpu_roots(ace, data, off, [4]), oracle.merkle_roots(data, off, [4]))
+
+
+def test_more_trees_than_one_launch_takes(ace):
+    """2^23 + 3 trees without leaves but for five of one leaf: a workgroup of 512
+    threads per tree is more than the 2^32 threads of one launch."""
+    import ctypes
+    import hashlib
+    import torch
+    n = (1 << 23) + 3
+    note("merkle %d trees" % n)
+    leaf = torch.arange(37, dtype=torch.uint8, device="cuda")
+    off = torch.tensor([0, 37], device="cuda")
+    roots = torch.zeros((n, 32), dtype=torch.uint8, device="cuda")
+    with_leaf = [0, (1 << 22) - 1, 1 << 22, (1 << 23) - 1, n - 1]
+    tree = np.zeros((n, 4), np.uint64)   # d_data, d_off, n_leaves, d_root_out
+    tree[:, 3] = roots.data_ptr() + 32 * np.arange(n, dtype=np.uint64)
+    tree[with_leaf, :3] = (leaf.data_ptr(), off.data_ptr(), 1)
+    arr = tree.ctypes.data_as(ctypes.POINTER(ace.ace_merkle_tree))
+    lib = ace.load()
+    ws = ace.workspace(lib.ace_merkle_workspace_size(arr, n))
+    rc = lib.ace_merkle_roots(arr, n, ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    assert rc == ace.ACE_OK, lib.ace_last_error()
+    torch.cuda.synchronize()
+    digest = lambda b: torch.frombuffer(bytearray(hashlib.sha256(b).digest()), dtype=torch.uint8).cuda()
+    want = digest(b"").repeat(n, 1)
+    want[with_leaf] = digest(bytes(range(37)))
+    assert torch.equal(roots, want)

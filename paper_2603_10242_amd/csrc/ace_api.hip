@@ -201,6 +201,7 @@ struct Plan {
     bool persistent;
     bool rev;
     uint32_t flags;
+    bool open;    // the library picks the form (the flags ask for none, or only fix the layout)
     bool attest;  // paper-form records (payload binding + credential over obj_hash || domain)
     uint32_t n_blocks;
     uint64_t total_tx;
@@ -223,6 +224,7 @@ int check_keyset(const ace_keyset *keys, uint32_t flags, Plan &p)
     if (keys->kind != ACE_KEYS_MIDSTATE && keys->kind != ACE_KEYS_REV)
         return fail(ACE_ERR_INVALID_ARG, "unknown keyset kind %d", keys->kind);
     p.flags = flags;
+    p.open = !(flags & (ACE_ORDERED | ACE_BUCKETED));
     p.rev = keys->kind == ACE_KEYS_REV;
     p.per_tx = (flags & ACE_PER_TX_KEYS) != 0;
     if (p.per_tx && !p.rev)
@@ -479,9 +481,9 @@ Form form_of(const Plan &p, uint64_t waves, unsigned cus, bool fork)
 {
     if (p.mode == kBinned && (p.persistent || p.per_tx)) return kGlobalBins;
     if (p.mode == kBinned && p.rev && fork && !p.attest && waves > 64ull * cus) return kGlobalBins;
-    if ((p.flags & ACE_ORDERED) || p.per_tx) return kInOrder;
+    if ((!p.open && (p.flags & ACE_ORDERED)) || p.per_tx) return kInOrder;
     if (waves > 2ull * cus * kLocalUnits) return p.mode == kBinned ? kGlobalBins : kLocal;
-    if (p.flags & ACE_BUCKETED) return kLocal;
+    if (!p.open) return kLocal;
     return waves <= 4ull * cus ? kInOrder : kLocal;
 }
 
@@ -562,7 +564,7 @@ int enqueue_stages(const Plan &p, const Batch &bt, const ace_keyset *keys, const
     // In the binned form the derivation (VALU-bound) runs on a second stream
     // beside the binning passes (memory-bound), which do not depend on it; the
     // verify kernel waits for both.
-    const bool per_tx = p.per_tx || (p.rev && form == kInOrder && !(p.flags & ACE_ORDERED));
+    const bool per_tx = p.per_tx || (p.rev && form == kInOrder && p.open);
     unsigned long long *const zero = graph || p.n_blocks > 1 ? nullptr : bt.one.count;  // else cleared already
     // in order with two waves per wave tile while each wave has its SIMD to itself
     const bool pairs = form == kInOrder && waves <= pair_verify_tiles();
@@ -1082,13 +1084,17 @@ int run_plan(const Plan &p, const ace_keyset *keys, const ace_block *blocks, uin
     return enqueue_stages(p, bt, keys, hp, ws, s, prof, false, !noalloc);
 }
 
+// `open`: ACE_ORDERED or ACE_BUCKETED fix the workspace layout only, and the form
+// is an open call's (the serving engine sizes a batch's workspace before it calls).
 int verify_impl(const ace_keyset *keys, const ace_block *blocks, uint32_t n_blocks,
-                void *d_workspace, size_t ws_bytes, uint32_t flags, void *stream, bool attest)
+                void *d_workspace, size_t ws_bytes, uint32_t flags, void *stream, bool attest,
+                bool open = false)
 {
     clear_error();
     Plan p{};
     int rc = make_plan(keys, blocks, n_blocks, flags, p, attest);
     if (rc) return rc;
+    p.open |= open;
     if (n_blocks == 0) return ACE_OK;
     if (!d_workspace) return fail(ACE_ERR_INVALID_ARG, "d_workspace is NULL");
     if (!aligned(d_workspace, 256)) return fail(ACE_ERR_INVALID_ARG, "d_workspace not 256-byte aligned");

@@ -118,7 +118,8 @@ class Backend {
     virtual int begin_slot(int slot) = 0;
     virtual int h2d(int slot, void *dst, const void *src, size_t n) = 0;
     // `flags` is chosen once per batch and passed to both calls, so the
-    // workspace sized for a batch is the one its verify call needs
+    // workspace sized for a batch is the one its verify call needs (which
+    // takes an open call's form on it)
     virtual int verify(int slot, const ace_block *blocks, uint32_t n_blocks, void *ws,
                        size_t ws_bytes, uint32_t flags) = 0;
     virtual size_t ws_size(const ace_block *blocks, uint32_t n_blocks, uint32_t flags) = 0;
@@ -184,7 +185,7 @@ class HipBackend : public Backend {
     int verify(int slot, const ace_block *blocks, uint32_t n_blocks, void *ws, size_t ws_bytes,
                uint32_t flags) override
     {
-        return ace_verify_batch(&keys_, blocks, n_blocks, ws, ws_bytes, flags, streams_[slot]);
+        return verify_impl(&keys_, blocks, n_blocks, ws, ws_bytes, flags, streams_[slot], false, true);
     }
     int d2h(int slot, void *dst, const void *src, size_t n) override
     {
@@ -442,9 +443,10 @@ bool admit(ace_stream *s)
         ++m;
     }
     // largest prefix whose arena range (inputs, outputs, workspace) and result
-    // area fit now.  The launch form (in-order or binned) is fixed here from
-    // one reading of the tuning and passed to both the workspace size and the
-    // verify call, so a tuning change in between cannot make them disagree.
+    // area fit now.  The workspace layout (an open call's: with the binning
+    // arrays from binned_min_tx on) is fixed here from one reading of the tuning
+    // and passed to both the workspace size and the verify call, so a tuning
+    // change in between cannot make them disagree.
     const ace_tuning tn = tuning();
     std::vector<ace_block> blocks;
     size_t arena_off = 0, arena_bytes = 0, in_total = 0, out_total = 0;
@@ -468,10 +470,8 @@ bool admit(ace_stream *s)
             bk.d_count_out = reinterpret_cast<uint64_t *>(fake);
             bk.n_tx = r->n;
         }
-        // (sorted beyond one wave per SIMD, as an open call is)
         vflags = m_tx >= tn.binned_min_tx ? (ACE_BUCKETED | (tn.auto_persistent ? ACE_PERSISTENT : 0u))
-                 : m_tx > 256ull * (unsigned)cu_count() ? ACE_BUCKETED
-                                                        : ACE_ORDERED;
+                                          : ACE_ORDERED;
         const size_t ws = align_up(s->be->ws_size(blocks.data(), (uint32_t)m, vflags), 256);
         arena_bytes = in_total + align_up(out_total, 256) + ws;
         if (ws && s->arena_alloc.alloc(arena_bytes, arena_off)) break;

@@ -123,3 +123,27 @@ def test_plain_form(ace, pool):
     st = s.stats()
     assert st["batches"] == 40 and st["max_batch_requests"] == 1
     s.close()
+
+
+def test_sorted_batch_takes_no_binning_arrays(ace, pool):
+    """Two requests that together have more transactions than run in order but fewer
+    than binned_min_tx, in an arena with room for their arrays and results and not for
+    the global bins' 28 bytes per transaction: they share a batch."""
+    import torch
+    reqs = [(0, 35_000), (20_000, 55_000)]
+    assert 70_000 < ace.get_tuning()["binned_min_tx"]
+    arrays = sum(int(pool.off[hi] - pool.off[lo]) + 44 * (hi - lo) for lo, hi in reqs)
+    note("stream tight arena")
+    ks = ace.midstate_keyset(ace.to_device(pool.rev), pool.salt, pool.info)
+    arena = torch.empty(arrays + (128 << 10), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    s = ace.Stream.create(ks, arena, staging_bytes=64 << 20, max_inflight=1)
+    # one long message holds the only slot (a chain of 65,537 blocks, about 150 ms) until both wait
+    size = 4 << 20
+    held = s.submit(np.zeros(size, np.uint8), np.array([0, size], np.uint64), np.zeros(1, np.uint32),
+                    np.zeros((1, 32), np.uint8))
+    tickets = [submit(s, pool, lo, hi) for lo, hi in reqs]
+    assert s.result(held)[1] == 0
+    check(s, pool, reqs, tickets)
+    assert s.stats()["max_batch_requests"] == 2
+    s.close()

@@ -372,3 +372,189 @@ def test_derive_at_shape_edges(ace, n_id, n_streams):
     ace.derive_keys_multi(d_rev, streams, key_out=keys)
     for k, (salt, info) in enumerate(streams):
         check(keys[k], None, salt, info)
+
+
+def with_faults(w_off, ids, n_id, n):
+    """Offsets and identities with, per 640 transactions, one that starts past its end
+    at a tile's first place (its neighbours read past their own ends, and the next one
+    starts below the tile's first offset), one in the middle of a tile, and one
+    unregistered."""
+    off, ids = w_off.copy(), ids.copy()
+    for at in range(64, n - 4, 640):
+        off[at] = off[at + 1] + 5
+    for at in range(300, n - 4, 640):
+        off[at] = off[at + 1] + 3
+    ids[7::640] = n_id + 2
+    return off, ids
+
+
+# sizes of calls that are sorted within workgroups, few and many tiles each
+@pytest.mark.parametrize("n", [700, 5_000, 70_000, 300_001])
+@pytest.mark.parametrize("form", ["hmac", "attest"])
+def test_local_form_with_faulty_offsets(ace, n, form):
+    import torch
+    attest = form == "attest"
+    n_id = 500
+    w, msg, off, tags, salt = (attestations if attest else sweep)(n, n_id, 1, n + 11)
+    off, ids = with_faults(off, w.ids, n_id, n)
+    print("%s n=%d" % (form, n), flush=True)
+    mask, count = (oracle.verify_attest if attest else oracle.verify_batch)(w.keys, msg, off, ids, tags, 8)
+    blk = ace.upload_block(None, off, ids, tags, msg_dev=ace.to_device(msg), record_bytes=72 if attest else 32)
+    blk.bitmask.fill_(-1)
+    ks = ace.midstate_keyset(ace.to_device(w.rev), salt, w.info)
+    (ace.verify_attestations if attest else ace.verify_batch)(ks, [blk], flags=ace.ACE_BUCKETED)
+    torch.cuda.synchronize()
+    m, c = blk.result()
+    assert c == count and np.array_equal(m, mask)
+
+
+@pytest.mark.parametrize("keys", ["midstate", "rev"])
+@pytest.mark.parametrize("wide", [False, True])
+def test_global_bins_of_small_replays(ace, keys, wide):
+    """A graph whose maxima are beyond the local form, replayed for small batches:
+    the binned kernel of large calls over wide records, faulty offsets, unregistered
+    identities, unaligned messages and uneven blocks."""
+    import torch
+    n, n_id = 6_000, 700
+    w = W.generate("bins", 77, n=n, n_id=n_id, lengths=lambda r, k: r.choice([0, 1, 55, 56, 64, 119, 200, 1_232, 5_000], k),
+                   p_invalid=0.02, kinds=(W.KIND_TAG, W.KIND_KEY))
+    off, ids = with_faults(w.off, w.ids, n_id, n)
+    lead = 3  # no message is 4-byte aligned by itself
+    d_msg = ace.to_device(np.concatenate([np.zeros(lead, np.uint8), w.msg]))
+    old = ace.set_tuning(wide_min_len=200) if wide else None
+    try:
+        make = ace.midstate_keyset if keys == "midstate" else ace.rev_keyset
+        g = ace.Graph(make(ace.to_device(w.rev), w.salt, w.info), 400, 2_200_000, ace.ACE_BUCKETED)
+    finally:
+        if wide:
+            ace.set_tuning(**old)
+    for cuts in ([0, n], [0, 1, 1, 65, 300, 301, 5_000, n], [2_000, 2_063], list(range(0, n + 1, 30))):
+        print("%s wide=%s blocks=%d" % (keys, wide, len(cuts) - 1), flush=True)
+        blocks = [ace.upload_block(None, off[a:b + 1] + np.uint64(lead), ids[a:b], w.tags[a:b], msg_dev=d_msg)
+                  for a, b in zip(cuts[:-1], cuts[1:])]
+        for blk in blocks:
+            blk.bitmask.fill_(-1)
+            blk.count.fill_(99)
+        for _ in range(2):
+            g.launch(blocks)
+        torch.cuda.synchronize()
+        for blk, a, b in zip(blocks, cuts[:-1], cuts[1:]):
+            m, c = blk.result()
+            mask, count = oracle.verify_batch(w.keys, w.msg, off[a:b + 1], ids[a:b], w.tags[a:b], 8)
+            assert c == count and np.array_equal(m, mask), (a, b)
+    g.close()
+
+
+@pytest.mark.parametrize("form", ["hmac", "attest"])
+def test_global_bins_of_many_small_blocks(ace, form):
+    """33,000 blocks of two transactions are more wave tiles than the local form takes."""
+    import torch
+    attest = form == "attest"
+    blocks_n, n_id = 33_000, 300
+    n = 2 * blocks_n
+    w, msg, off, tags, salt = (attestations if attest else sweep)(n, n_id, 1, 5)
+    off, ids = with_faults(off, w.ids, n_id, n)
+    print("%s blocks=%d" % (form, blocks_n), flush=True)
+    d_msg, d_off, d_ids, d_tags = (ace.to_device(x) for x in (msg, off, ids.astype(np.uint32), tags))
+    mask = torch.full((blocks_n,), -1, dtype=torch.int32, device="cuda")
+    count = torch.full((blocks_n,), 99, dtype=torch.int64, device="cuda")
+    blocks = [ace.DeviceBlock(d_msg, d_off[2 * b:2 * b + 3], d_ids[2 * b:2 * b + 2], d_tags[2 * b:2 * b + 2],
+                              mask[b:b + 1], count[b:b + 1], 2) for b in range(blocks_n)]
+    ks = ace.midstate_keyset(ace.to_device(w.rev), salt, w.info)
+    (ace.verify_attestations if attest else ace.verify_batch)(ks, blocks, flags=ace.ACE_BUCKETED)
+    torch.cuda.synchronize()
+    # a block's message area ends at its own last offset, which changes no verdict
+    omask, ocount = (oracle.verify_attest if attest else oracle.verify_batch)(w.keys, msg, off, ids, tags, 8)
+    bits = np.unpackbits(omask.view(np.uint8), bitorder="little")[:n].reshape(-1, 2)
+    assert np.array_equal(mask.cpu().numpy().view(np.uint32), bits[:, 0] + 2 * bits[:, 1])
+    assert np.array_equal(count.cpu().numpy(), bits.sum(1)) and ocount == bits.sum()
+
+
+# captured forms of up to two waves per CU's tile, of one wave per SIMD, and the same on request
+@pytest.mark.parametrize("max_blocks,max_tx", [(8, 2_000), (16, 50_000)])
+@pytest.mark.parametrize("keys", ["midstate", "rev"])
+@pytest.mark.parametrize("ordered", [False, True])
+def test_small_graphs(ace, max_blocks, max_tx, keys, ordered):
+    """Graphs that hold no more than a wave per SIMD, replayed at their maxima, for
+    fewer transactions and blocks, for none, and at the maxima again."""
+    import torch
+    n_id = 900
+    w, msg, off, tags, salt = sweep(max_tx, n_id, 1, max_tx)
+    off, ids = with_faults(off, w.ids, n_id, max_tx)
+    make = ace.midstate_keyset if keys == "midstate" else ace.rev_keyset
+    g = ace.Graph(make(ace.to_device(w.rev), salt, w.info), max_blocks, max_tx, ace.ACE_ORDERED if ordered else 0)
+    d_msg = ace.to_device(msg)
+    full = [max_tx * k // max_blocks for k in range(max_blocks + 1)]
+    for cuts in ([0, max_tx], full, [5, 6], [0, 0], [0, 64, 64, 65, 1_500], [100, 164], full):
+        print("graph %d/%d %s ordered=%s blocks=%d" % (max_blocks, max_tx, keys, ordered, len(cuts) - 1), flush=True)
+        blocks = [ace.upload_block(None, off[a:b + 1], ids[a:b], tags[a:b], msg_dev=d_msg)
+                  for a, b in zip(cuts[:-1], cuts[1:])]
+        for blk in blocks:
+            blk.bitmask.fill_(-1)
+            blk.count.fill_(99)
+        for _ in range(2):
+            g.launch(blocks)
+            ace.verify_batch(make(ace.to_device(w.rev), salt, w.info), blocks[:1])  # other work between replays
+        for blk in blocks:
+            blk.count.fill_(99)
+        g.launch(blocks)
+        torch.cuda.synchronize()
+        for blk, a, b in zip(blocks, cuts[:-1], cuts[1:]):
+            m, c = blk.result()
+            mask, count = oracle.verify_batch(w.keys, msg, off[a:b + 1], ids[a:b], tags[a:b], 8)
+            assert c == count and np.array_equal(m, mask), (a, b)
+    g.close()
+
+
+@pytest.mark.parametrize("n_blocks", [1_023, 1_024, 1_025, 2_049, 5_000])
+def test_graph_plan_of_many_blocks(ace, n_blocks):
+    """The plan kernel scans 1,024 blocks at a time: prefixes of one, two, three and
+    five passes, empty blocks among them."""
+    import torch
+    n_id = 300
+    r = np.random.default_rng(n_blocks)
+    sizes = r.integers(0, 4, n_blocks)
+    sizes[n_blocks // 2] = 500
+    n = int(sizes.sum())
+    w, msg, off, tags, salt = sweep(n, n_id, 1, 9)
+    print("plan blocks=%d tx=%d" % (n_blocks, n), flush=True)
+    g = ace.Graph(ace.midstate_keyset(ace.to_device(w.rev), salt, w.info), n_blocks, n)
+    d_msg, d_off, d_ids, d_tags = (ace.to_device(x) for x in (msg, off, w.ids.astype(np.uint32), tags))
+    cuts = np.concatenate([[0], np.cumsum(sizes)])
+    words = np.concatenate([[0], np.cumsum((sizes + 31) // 32)])
+    mask = torch.full((int(words[-1]) + 1,), -1, dtype=torch.int32, device="cuda")
+    count = torch.full((n_blocks,), 99, dtype=torch.int64, device="cuda")
+    blocks = [ace.DeviceBlock(d_msg, d_off[a:b + 1], d_ids[a:b], d_tags[a:b], mask[int(words[k]):int(words[k + 1])],
+                              count[k:k + 1], int(b - a)) for k, (a, b) in enumerate(zip(cuts[:-1], cuts[1:]))]
+    for some in (blocks, blocks[:7], blocks):
+        mask.fill_(-1)
+        count.fill_(99)
+        g.launch(some)
+    torch.cuda.synchronize()
+    omask, _ = oracle.verify_batch(w.keys, msg, off, w.ids, tags, 8)
+    bits = np.unpackbits(omask.view(np.uint8), bitorder="little")
+    got, counts = mask.cpu().numpy().view(np.uint32), count.cpu().numpy()
+    for k, (a, b) in enumerate(zip(cuts[:-1], cuts[1:])):
+        mine = bits[a:b]
+        assert counts[k] == mine.sum(), k
+        assert np.array_equal(got[words[k]:words[k + 1]], W.pack_bits(mine.astype(bool))[:(b - a + 31) // 32]), k
+    g.close()
+
+
+@pytest.mark.parametrize("n", [32_767, 32_768, 32_769])
+@pytest.mark.parametrize("keys", ["midstate", "rev"])
+def test_open_calls_at_the_pair_edge(ace, n, keys):
+    """512 wave tiles are the most that take two waves each on a 256-CU device."""
+    import torch
+    n_id = 2_000
+    w, msg, off, tags, salt = sweep(n, n_id, 1, n)
+    off, ids = with_faults(off, w.ids, n_id, n)
+    print("pair edge n=%d %s" % (n, keys), flush=True)
+    blk = ace.upload_block(msg, off, ids, tags)
+    blk.bitmask.fill_(-1)
+    make = ace.midstate_keyset if keys == "midstate" else ace.rev_keyset
+    ace.verify_batch(make(ace.to_device(w.rev), salt, w.info), [blk])
+    torch.cuda.synchronize()
+    mask, count = oracle.verify_batch(w.keys, msg, off, ids, tags, 8)
+    m, c = blk.result()
+    assert c == count and np.array_equal(m, mask)

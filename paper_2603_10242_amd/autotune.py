@@ -3,13 +3,15 @@
 Measures, on the device at hand, the candidates the library can run and
 installs the fastest through ace_set_tuning:
 
-* binned_min_tx: the batch size from which binning by block count beats the
-  in-order kernel (the binning passes cost a few launches; below this size
-  they do not pay);
+* binned_min_tx: the batch size from which sorting by block count (ACE_BUCKETED)
+  beats the in-order kernel (ACE_ORDERED).  An open call takes its form from its
+  wave tiles; from this size on its workspace has the arrays of the global bins,
+  which the largest calls and persistent ones run;
 * verify_wgs_per_cu ("tiles per CU"): workgroups per CU of the persistent
   verify kernel (and of the graph's in-order one), and whether the open mode
   should use the persistent kernel at all (auto_persistent);
-* aux_wgs_per_cu: workgroups per CU of the binning and finalize passes;
+* aux_wgs_per_cu: workgroups per CU of the global binning and finalize passes,
+  on a batch that runs them;
 * derive_wgs_per_cu: workgroups per CU of the key derivation while it runs on
   a second stream beside the binning passes (fewer leave room for them);
 * grab_cap, per length bucket (inner block count ranges): wave tiles the
@@ -131,6 +133,9 @@ def run(sizes=(4096, 16384, 65536, 262144, 1 << 20, 4 << 20), big: int = 4 << 20
     ace.load()
     torch.cuda.set_device(0)
     arch, cus = device_key()
+    # 128 wave tiles of 64 per CU are the most that are sorted within workgroups
+    if big <= 128 * 64 * cus:
+        raise ValueError("big: %d transactions do not reach the global bins (%d)" % (big, 128 * 64 * cus))
     default = ace.get_tuning()
     log("autotune on %s (%d CUs)" % (arch, cus))
     w = W.config3(n=max(max(sizes), big), n_id=1 << 18)
@@ -141,7 +146,7 @@ def run(sizes=(4096, 16384, 65536, 262144, 1 << 20, 4 << 20), big: int = 4 << 20
     def block(n):
         return ace.upload_block(None, w.off[: n + 1], w.ids[:n], w.tags[:n], msg_dev=d_msg)
 
-    # 1. in-order vs binned by batch size
+    # 1. in-order vs sorted by batch size
     crossover = None
     for n in sizes:
         blk = block(n)
@@ -179,7 +184,7 @@ def run(sizes=(4096, 16384, 65536, 262144, 1 << 20, 4 << 20), big: int = 4 << 20
     best_wpc = best[1]
     blk = blks[big]
 
-    # 3. binning and finalize passes: workgroups per CU
+    # 3. global binning and finalize passes: workgroups per CU
     ace.set_tuning(verify_wgs_per_cu=best_wpc)
     best_aux = (float("inf"), default["aux_wgs_per_cu"])
     for apc in (2, 4, 8, 16):

@@ -35,12 +35,15 @@ HBM_PEAK_GBS = 8000.0
 METRIC = "verified HMAC attestations/sec on 1 GPU; %peak INT32 VALU; p99 batch latency"
 
 
-def verify_kernel(n: int, mode: str) -> str:
-    """The verify kernel a single-block call of n transactions runs (ACE_BUCKETED
-    calls are sorted within workgroups up to 2^17 wave tiles of 64)."""
+def verify_kernel(n: int, mode: str, derived: bool, cus: int) -> str:
+    """The verify kernel a single-block call of n transactions runs on `cus` compute
+    units: in order with two waves per wave tile of 64 up to 2 tiles per CU;
+    ACE_BUCKETED sorted within workgroups up to 128 tiles per CU, 64 where a message
+    call derives its keys (`derived`); persistent calls always over the global bins."""
+    tiles = (n + 63) // 64
     if mode == "ordered":
-        return "k_verify_ordered" if (n + 63) // 64 > 512 else "k_verify_pair"
-    if mode == "binned" and (n + 63) // 64 <= 1 << 17:
+        return "k_verify_ordered" if tiles > 2 * cus else "k_verify_pair"
+    if mode == "binned" and tiles <= (64 if derived else 128) * cus:
         return "k_verify_local"
     return "k_verify_binned"
 
@@ -545,7 +548,8 @@ def bench_attest(args) -> dict:
                    "n_tx": w.n, "n_id": w.n_id, "ids": args.ids,
                    "payload": "uniform 130..154 B", "record": "obj_hash || domain || credential",
                    "mode": args.mode, "invalid": int(w.n - w.truth.sum())},
-        "roofline": {"kernel": verify_kernel(w.n, args.mode),
+        "roofline": {"kernel": verify_kernel(w.n, args.mode, False,
+                                             torch.cuda.get_device_properties(0).multi_processor_count),
                      "bound": "alu", "achieved": achieved, "peak": PEAK_INT32_TOPS,
                      "unit": "T int32 lane-instr/s", "frac": achieved / PEAK_INT32_TOPS,
                      "traffic": None,
@@ -1005,7 +1009,8 @@ def main() -> int:
                     if args.keys == "recomputed" else "resident midstates",
         },
         "roofline": {
-            "kernel": verify_kernel(w.n, args.mode),
+            "kernel": verify_kernel(w.n, args.mode, args.keys == "recomputed",
+                                    torch.cuda.get_device_properties(0).multi_processor_count),
             "bound": "alu",
             "achieved": achieved,
             "peak": PEAK_INT32_TOPS,

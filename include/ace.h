@@ -73,8 +73,8 @@ typedef enum {
 #define ACE_PERSISTENT 0x4u /* fixed grid of workgroups pulling wave tiles from a counter */
 #define ACE_PER_TX_KEYS 0x8u /* keyset of kind ACE_KEYS_REV: derive each transaction's key
                                 inside the verify kernel instead of once per identity */
-/* Neither ORDERED nor BUCKETED: the library picks (in order while a wave per SIMD
-   holds the call, grouped beyond). */
+/* Neither ORDERED nor BUCKETED: the library picks (in order while one wave per SIMD
+   holds the call, grouped beyond: within workgroups, or over the whole call). */
 
 /* Keyset kinds. */
 #define ACE_KEYS_MIDSTATE 0 /* d_mid[n_id][16]: cached HMAC midstates (from ace_derive_keys) */
@@ -229,13 +229,16 @@ ACE_API int ace_verify_batch_noalloc(const ace_keyset *keys, const ace_block *bl
  * candidates on the device and installs the fastest with ace_set_tuning.
  *   binned_min_tx      batches of at least this many transactions are laid out
  *                      as ACE_BUCKETED ones when the caller leaves the mode
- *                      open (smaller ones may still be sorted by block count
- *                      within workgroups, which needs no workspace)
+ *                      open, with room for the global bins (smaller ones may
+ *                      still be sorted by block count within workgroups, which
+ *                      needs no workspace)
  *   verify_wgs_per_cu  workgroups per CU of the persistent verify kernel and
  *                      of the graph's in-order verify ("tiles per CU")
  *   aux_wgs_per_cu     workgroups per CU of the global binning and finalize
- *                      passes (batches of more than 2^17 wave tiles of 64
- *                      transactions, and persistent ones)
+ *                      passes (grouped batches of more than 128 wave tiles of
+ *                      64 transactions per CU, of more than 64 where keys are
+ *                      derived in an ace_verify_batch call, and persistent and
+ *                      per-transaction-key ones)
  *   auto_persistent    1: binned batches in the open mode use the persistent
  *                      verify kernel
  *   derive_wgs_per_cu  workgroups per CU of the key derivation while it runs
@@ -280,8 +283,10 @@ ACE_API int ace_set_tuning(const ace_tuning *t);
  * mix of block count, block sizes and message lengths within the maxima.
  * Every grid is fixed: the verify kernel is launched for the largest batch
  * (surplus workgroups exit at once) or, with ACE_PERSISTENT, as the persistent
- * kernel; the in-order form (flag ACE_ORDERED) is a grid-stride kernel.  The launch tuning in force at ace_graph_create is captured with
- * the graph; later ace_set_tuning calls do not change its replays.
+ * kernel; the in-order form (flag ACE_ORDERED, and open graphs of at most one
+ * wave per SIMD) is a grid-stride kernel.  The launch tuning in force at
+ * ace_graph_create is captured with the graph; later ace_set_tuning calls do not
+ * change its replays.
  *   d_workspace  at least ace_graph_workspace_size() bytes, 256-byte aligned,
  *                owned by the graph until ace_graph_destroy.
  * ace_graph_launch enqueues one replay on `stream` for the given blocks (the

@@ -61,7 +61,7 @@ __host__ __device__ inline LocalShare local_share(uint64_t waves, uint32_t slots
 // input ordered by message length, with its long messages in one place or in
 // alternating runs, gives every workgroup about the same work.  One consecutive
 // share each, 1M transactions took 812 us sorted by length and 770 with the long
-// ones in one place; dealt out 249 and 154 (shuffled 248 and 150).
+// ones in one place; dealt out 241 and 154 (shuffled 243 and 140).
 //   tiles per deal   four where a workgroup has four to eight, one for each SIMD
 //                    of its CU (a long message's chain takes the time there, and
 //                    tiles apart cost it 4 us of 74), else two: the balance of
@@ -73,7 +73,7 @@ __host__ __device__ inline LocalShare local_share(uint64_t waves, uint32_t slots
 //                    tried the one that spreads long and short runs of equal
 //                    length (1/128 of a deal to eight of them) most evenly; with
 //                    the same start every time, 1M transactions in runs of 128
-//                    tiles took 540 us against 350.
+//                    tiles took 540 us against 360 (shuffled 341).
 struct LocalTiles {
     uint32_t first_tile, slot, slots, shift, dealt, count;
 };

@@ -519,9 +519,12 @@ __device__ __forceinline__ bool load_tx(const DevBlock &d, uint64_t i, const Key
 // one block; the ballot is that block's two bitmask words, its population
 // count goes to the block's count (cleared before).
 //
-// Bound by one wave's chain of compressions: it serves calls of at most one
-// wave per SIMD (and ACE_ORDERED), where a lone wave issues a VALU instruction
-// every 4.3 cycles, so whatever it waits for besides costs the call its time.
+// Bound by one wave's chain of compressions: open calls of at most one wave per
+// SIMD take it, where a lone wave issues a VALU instruction every 4.3 cycles, so
+// whatever it waits for besides costs the call its time.  ACE_ORDERED takes it at
+// any size: loading a block ahead instead of three at a time costs nothing there
+// (1M lognormal lengths 756 us against 763, 8M 5,365 against 5,370; keys per
+// transaction, 3M 2,873 against 3,027).
 // ------------------------------------------------------------------------------------------
 template <bool PER_TX_KEYS, bool ATTEST>
 __global__ void __launch_bounds__(kWG) ACE_WAVES(4) k_verify_ordered(Batch bt, KeySource ks, HkdfParams hp)
@@ -716,9 +719,10 @@ __global__ void __launch_bounds__(128) k_verify_pair(Batch bt, KeySource ks, Hkd
 // the globally binned verify (count, scan, scatter, finalize, count and their
 // 56 bytes per transaction; 39 us of 257 for 1M transactions).  What it gives
 // up: sorting 4,096 transactions fills 97.7% of the sweep's lanes instead of
-// 99.9% (2,048: 95.3%), and a CU's share is fixed.  8,192 per workgroup measured
-// slower (16M transactions +4%: the messages in flight spread over twice the
-// memory), 2,048 no faster.
+// 99.9% (2,048: 95.3%), and a CU's share is fixed, so it serves calls that one
+// round of workgroups takes, with the tiles dealt out among them.  8,192 per
+// workgroup measured slower (16M transactions +4%: the messages in flight spread
+// over twice the memory), 2,048 no faster.
 // ------------------------------------------------------------------------------------------
 // Waves of one SIMD at four priorities, the first tiles' (the longest) highest.
 // At equal ones they go through their tiles in step and wait for memory

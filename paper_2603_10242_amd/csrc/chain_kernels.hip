@@ -80,9 +80,8 @@ __global__ void __launch_bounds__(kWG) ACE_WAVES(8) k_poh_verify(const uint8_t *
     poh_result(h, live, i, i0, n, end, bitmask, count, false);
 }
 
-// Two waves per 64 segments (pair_kernels.hip), for up to half as many wave tiles
-// as there are SIMDs.  `solo`: the call is one workgroup, which stores the count
-// itself.
+// Two waves per 64 segments (pair_kernels.hip), for up to one wave tile per CU.
+// `solo`: the call is one workgroup, which stores the count itself.
 __global__ void __launch_bounds__(128) k_poh_pair(const uint8_t *__restrict__ start,
                                                   const uint8_t *__restrict__ end,
                                                   const uint32_t *__restrict__ steps,

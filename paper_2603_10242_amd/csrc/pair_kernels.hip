@@ -12,7 +12,8 @@
 //
 // Bound by that chain: a lone wave takes 2.5 us for a whole compression and
 // about 1.8 for the first wave's part.  It needs two waves' SIMDs per 64 lanes,
-// so it serves up to half as many wave tiles as there are SIMDs.
+// so it serves up to half as many wave tiles as there are SIMDs (verify), or one
+// per CU (derivations and hash chains, whose waves meet every sixteen rounds).
 //
 //   k_derive_pair    64 identities of one (salt, info) stream per workgroup.
 //   k_poh_pair       64 hash-chain segments per workgroup.

@@ -66,3 +66,16 @@ def test_block_descriptor_checked_once_and_rechecked_after_reassignment(lib, mon
         blk.struct()
     blk.bitmask = torch.zeros(4, dtype=torch.int32)
     assert blk.struct().d_bitmask_out == blk.bitmask.data_ptr()
+
+
+def test_bench_labels_follow_the_dispatch():
+    """bench.py names the verify kernel that a call of its size and mode runs."""
+    import bench
+    label = lambda n, mode, derived=False: bench.verify_kernel(n, mode, derived, 256)
+    assert label(32_768, "ordered") == "k_verify_pair"
+    assert label(32_769, "ordered") == "k_verify_ordered"
+    assert label(2_097_152, "binned") == "k_verify_local"
+    assert label(2_097_153, "binned") == "k_verify_binned"
+    assert label(1_048_576, "binned", True) == "k_verify_local"
+    assert label(4 << 20, "binned", True) == "k_verify_binned"
+    assert label(5_000, "binned-persistent") == "k_verify_binned"

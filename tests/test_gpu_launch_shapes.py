@@ -237,8 +237,8 @@ def test_time_of_ordered_lengths(ace, n, order):
 @pytest.mark.parametrize("n", [1_000_000, 8_000_000])
 def test_time_of_a_few_long_messages(ace, n):
     """One message of 20,000 bytes among 2,048 of 100: its chain of 313 blocks is
-    waited for once, at most half as long again, whatever the call's size (sorted in
-    four rounds of workgroups, 8M transactions waited four times)."""
+    waited for once, at most three quarters as long again, whatever the call's size
+    (sorted in four rounds of workgroups, 8M transactions waited four times)."""
     import torch
     L = torch.full((n,), 100, dtype=torch.int64, device="cuda")
     short = time_of_lengths(ace, L, 3)
@@ -246,8 +246,8 @@ def test_time_of_a_few_long_messages(ace, n):
     chain = time_of_lengths(ace, L[1000:1001], 3)
     mixed = time_of_lengths(ace, L, 3)
     print("n=%d: %.0f us, all short %.0f, one long message alone %.0f" % (n, mixed, short, chain), flush=True)
-    # the long messages' own blocks are a tenth of the others'
-    assert mixed <= 1.2 * short + 1.5 * chain
+    # the long messages' own blocks are a twentieth of the others'
+    assert mixed <= 1.2 * short + 1.75 * chain
 
 
 @pytest.mark.parametrize("n", [100_000, 200_000])
